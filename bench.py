@@ -68,6 +68,10 @@ def algorithmic_ops_per_pixel(dtype_code: int, k: int, kh: int | None = None):
     (max of minima, median of medians, min of maxima, median of the three);
     these are 32-bit lane-ops, one element each.
 
+    Sliding histograms (data-aware form 3): no min/max; "hist" in place of
+    the packed flag and the LDS counter updates per pixel, 2 (kw + 3) per
+    group of four pixels.
+
     Data-aware: two lane-ops per merge output (the compare that picks the
     smaller head and the min that produces it) plus two per compare-exchange
     of the per-lane sorting networks (min and max), from the schedule; the
@@ -75,7 +79,7 @@ def algorithmic_ops_per_pixel(dtype_code: int, k: int, kh: int | None = None):
     from paper_2507_19926_amd import _lib, dagen, netgen as ng
     if kh is not None and kh != k:
         variant, tw, th = _lib.query_rect_config(dtype_code, k, kh)
-        form = 0
+        form = 3 if variant == _lib.MF_VARIANT_DATA_AWARE and dtype_code == _lib.MF_U8 and k >= 3 else 0
     else:
         kh = k
         variant, tw, th, _, form, _ = _lib.query_options(dtype_code, k)
@@ -87,6 +91,8 @@ def algorithmic_ops_per_pixel(dtype_code: int, k: int, kh: int | None = None):
         net = ng.op_counts(P)["minmax"] / (tw * th)
         srt = ng.op_counts(ng.build_sort_program(kh - th + 1))["minmax"] / th
         return variant, (tw, th), net + srt, packed
+    if form == 3:
+        return variant, (1, 1), 2.0 * (k + 3) / 4.0, "hist"
     st = dagen.schedule(k, tw, th, kh=kh).stats
     return variant, (tw, th), 2.0 * (st["per_pixel_outputs"] + st["per_pixel_sort_ces"]), False
 
@@ -119,6 +125,12 @@ def roofline(dtype_code: int, k: int, pixels_per_launch: int, launch_s: float, k
     es = {0: 1, 1: 2, 2: 4, 3: 4}[dtype_code]
     bytes_per_launch = 2 * es * pixels_per_launch
     variant, tile, ops_px, packed = algorithmic_ops_per_pixel(dtype_code, k, kh)
+    if packed == "hist":
+        # a counter update reads and writes one LDS word
+        achieved = 8.0 * ops_px * pixels_per_launch / launch_s
+        return {"bound": "lds", "achieved": achieved / 1e12, "peak": LDS_PEAK_BPS / 1e12, "unit": "TB/s",
+                "frac": achieved / LDS_PEAK_BPS, "traffic": None, "lds_updates_per_pixel": ops_px,
+                "variant": variant, "tile": list(tile)}
     valu_peak = VALU_LANES_PER_S * (2 if packed else 1)    # element-ops/s
     t_hbm = bytes_per_launch / HBM_PEAK_BPS
     t_alu = (ops_px * pixels_per_launch / valu_peak) if ops_px else 0.0

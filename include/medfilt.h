@@ -142,7 +142,8 @@ int32_t mf_max_rect_side(void);
  * kw == kh answers as mf_query_config with default options; otherwise
  * MF_VARIANT_OBLIVIOUS and the network's root tile when one is compiled for
  * the shape, else MF_VARIANT_DATA_AWARE and the generated schedule's tile
- * (the MF_VARIANT_AUTO choice). Errors as
+ * (the MF_VARIANT_AUTO choice; MF_U8 runs such shapes by sliding histograms,
+ * MF_VARIANT_DATA_AWARE runs the schedule for every dtype). Errors as
  * median_filter_rect's window and dtype checks (MF_ERR_NULL for a NULL
  * output pointer). */
 int32_t mf_query_rect_config(int32_t dtype, int32_t kw, int32_t kh, int32_t* variant,

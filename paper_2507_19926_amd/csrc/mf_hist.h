@@ -1,0 +1,26 @@
+// Sliding-histogram form of the median filter for 8-bit planes (mf_hist.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "mf_internal.h"
+
+// Form number of the data-aware variant in mf_options.
+constexpr int kDaFormHist = 3;
+
+// Everything the host needs of one window's kernels.
+struct HistKernelInfo {
+    const void* planes;
+    const void* batched;    // null where no square window uses it
+    int threads, cols, rows;   // output columns of a work-group; rows of a batched block
+    size_t lds;
+};
+
+// Whether the kw x kh window (kw columns, kh rows, both odd) has a kernel.
+bool mf_hist_supports(int dtype, int kw, int kh);
+// `planes` planes of H x W, plane p at src/dst + p * plane_stride bytes.
+hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plane_stride, int H, int W,
+                          long long pitch, int kw, int kh, hipStream_t stream);
+// Batched kernel of the square k x k window (arguments: jobs, njobs, nblocks).
+hipError_t mf_hist_batched(int k, MfBatchedKernel* kern);

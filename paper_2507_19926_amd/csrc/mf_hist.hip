@@ -1,0 +1,119 @@
+// Sliding-histogram form: choice of kernel and launch (the kernels are
+// described in mf_hist_kernel.h).
+#include <atomic>
+
+#include "mf_hist_kernel.h"
+
+// P = 1 and P = 2 kernels of the windows up to 31 columns, P = 2 from 33 on
+// (mf_hist_p1.hip, mf_hist_p2.hip, mf_hist_wide.hip).
+bool mf_hist_kernel_p1(int kw, HistKernelInfo* k);
+bool mf_hist_kernel_p2(int kw, HistKernelInfo* k);
+bool mf_hist_kernel_wide(int kw, HistKernelInfo* k);
+
+namespace {
+
+constexpr int kMaxDevices = 64;
+
+// All counts of the window fit the one-word layout: 4 bits for a column's
+// kh values, 8 for the kw - 3 shared columns'.
+bool one_word(int kw, int kh) { return kh <= 15 && kh * (kw - 3) <= 255; }
+
+bool find(int kw, int kh, HistKernelInfo* k)
+{
+    if (kw < 3 || kw % 2 == 0 || kh < 1 || kh > 255) return false;
+    if (one_word(kw, kh) && kw <= 31) return mf_hist_kernel_p1(kw, k);
+    return kw <= 31 ? mf_hist_kernel_p2(kw, k) : mf_hist_kernel_wide(kw, k);
+}
+
+// The kernels take more than 64 KB of LDS, which has to be allowed once per
+// device and kernel.
+hipError_t allow_lds(const void* fn, int slot, int dev)
+{
+    static std::atomic<unsigned char> done[kMaxDevices][4 * 38];
+    if (done[dev][slot].load(std::memory_order_acquire)) return hipSuccess;
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e == hipSuccess) done[dev][slot].store(1, std::memory_order_release);
+    return e;
+}
+
+hipError_t device(int* dev, int* cus)
+{
+    static std::atomic<int> count[kMaxDevices];
+    hipError_t e = hipGetDevice(dev);
+    if (e != hipSuccess) return e;
+    if (*dev < 0 || *dev >= kMaxDevices) return hipErrorInvalidDevice;
+    *cus = count[*dev].load(std::memory_order_relaxed);
+    if (*cus == 0) {
+        e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, *dev);
+        if (e != hipSuccess) return e;
+        count[*dev].store(*cus, std::memory_order_relaxed);
+    }
+    return hipSuccess;
+}
+
+int slot_of(int kw, bool two, bool batched) { return (kw / 2) * 4 + (two ? 2 : 0) + (batched ? 1 : 0); }
+
+}  // namespace
+
+bool mf_hist_supports(int dtype, int kw, int kh)
+{
+    HistKernelInfo k;
+    return dtype == MF_U8 && find(kw, kh, &k);
+}
+
+hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plane_stride, int H, int W,
+                          long long pitch, int kw, int kh, hipStream_t stream)
+{
+    HistKernelInfo k;
+    if (!find(kw, kh, &k)) return hipErrorInvalidValue;
+    int dev = 0, cus = 0;
+    hipError_t e = device(&dev, &cus);
+    if (e != hipSuccess) return e;
+    e = allow_lds(k.planes, slot_of(kw, !(one_word(kw, kh) && kw <= 31), false), dev);
+    if (e != hipSuccess) return e;
+    const int ncol = (W + k.cols - 1) / k.cols;
+    // Strips of R rows: a strip costs its rows and, for its first window,
+    // about kh / 4 + 8 more; two work-groups run on each CU, so a launch of
+    // r full rounds of them is the cheapest for its r.
+    const long long slots = 2LL * cus, per_strip = (long long)ncol * planes;
+    const long long first = kh / 4 + 8;
+    long long best = -1;
+    int R = H;
+    for (int r = 1; r <= 8; ++r) {
+        long long n = r * slots / per_strip;
+        if (n < 1) n = 1;
+        if (n > H) n = H;
+        const int rows = (int)((H + n - 1) / n);
+        const long long strips = (H + rows - 1) / rows;
+        const long long cost = ((strips * per_strip + slots - 1) / slots) * (rows + first);
+        if (best < 0 || cost < best) best = cost, R = rows;
+    }
+    const int ns = (H + R - 1) / R;
+    if ((long long)ncol * ns > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    for (int p0 = 0; p0 < planes; p0 += 65535) {     // grid rows are planes
+        const int np = planes - p0 < 65535 ? planes - p0 : 65535;
+        const unsigned char* s8 = (const unsigned char*)src + p0 * plane_stride;
+        unsigned char* d8 = (unsigned char*)dst + p0 * plane_stride;
+        void* args[] = {&s8, &d8, &H, &W, &pitch, &plane_stride, (void*)&ncol, &R, &kh};
+        e = hipLaunchKernel(k.planes, dim3((unsigned)(ncol * ns), np), dim3(k.threads), args, k.lds, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t mf_hist_batched(int k, MfBatchedKernel* kern)
+{
+    HistKernelInfo h;
+    if (!find(k, k, &h) || !h.batched) return hipErrorInvalidValue;
+    int dev = 0, cus = 0;
+    hipError_t e = device(&dev, &cus);
+    if (e != hipSuccess) return e;
+    e = allow_lds(h.batched, slot_of(k, !one_word(k, k), true), dev);
+    if (e != hipSuccess) return e;
+    kern->fn = h.batched;
+    kern->threads = h.threads;
+    kern->lds = h.lds;
+    kern->bw = h.cols;
+    kern->bh = h.rows;
+    return hipSuccess;
+}

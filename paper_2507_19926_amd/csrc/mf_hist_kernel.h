@@ -1,0 +1,376 @@
+// Sliding-histogram median of 8-bit planes (kernel templates; mf_hist.hip and
+// its parts instantiate them).
+//
+// A work-group walks down a strip of kCols output columns and keeps, in LDS,
+// the histogram of every column's window while the window slides by one row.
+// Neighbouring columns share their windows' inner columns, so four adjacent
+// columns form a group with one set of 256 counter words: the count of the
+// KW - 3 columns that all four windows hold, and the counts of the three
+// columns left (L0 L1 L2) and right (R0 R1 R2) of them; window w of the group
+// is the shared count and three consecutive ones of L0 L1 L2 R0 R1 R2, summed
+// by one or two dot products of the counter word. A row step costs
+// 2 (KW + 3) LDS atomics per group of four pixels whatever the data, against
+// the hundreds of merge outputs or min/max per pixel of the schedules and
+// networks, and no work grows with KW * KH.
+//
+// Counter words: P = 1 holds all seven counts in 32 bits (8 shared, six of 4;
+// windows of up to 15 rows and 255 shared values), 64 groups to a
+// work-group; P = 2 in 64 bits (16 shared, six of 8), 32 groups. Either way
+// 64 KB of counters, two work-groups per CU. A field may overflow between an
+// addition and the removal that follows it: words are added modulo 2^32, so
+// they are exact when read. Bin v of group g lies at 256 v + 128 p + 4 g:
+// the address of a pixel's counter is one v_perm_b32 (pixel byte above the
+// group's byte), and no two groups of a wave share an LDS bank.
+//
+// Half of the waves search, half slide the histogram, in turn (two barriers
+// a row). A search wave starts at the last median's bin: it knows how many
+// window values lie below that bin (the rows that came and went are counted
+// against it, four bytes at a time, by v_lerp_u8's carry) and walks up or
+// down from it, four bins and then eight at a time. A slide wave holds the
+// addresses of its counters ready while the others search.
+//
+// Bound: the row step's latency (a barrier, the dependent search, a barrier,
+// the atomics), overlapped between the two work-groups of a CU; from about
+// k = 50 on the LDS atomics (about 6 clocks for each wave's).
+#pragma once
+
+#include <type_traits>
+
+#include "mf_hist.h"
+
+namespace {
+
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+typedef __attribute__((address_space(3))) u32x4a4 lds_u32x4a4;
+
+constexpr int kT = 4;                 // output columns of a group
+constexpr uint32_t kPad = 1024;       // the search may read three counters past either end
+constexpr uint32_t kCounters = 65536;
+constexpr uint32_t kStage = kPad + kCounters + kPad;
+
+// Counter words of a group: P = 1: one, 64 groups to a work-group, bin v of
+// group g at 256 v + 4 g; P = 2: two, 32 groups, word p at 256 v + 128 p + 4 g.
+template <int KW, int P>
+struct Hist {
+    static constexpr int kGroups = 64 / P;
+    static constexpr int kCols = kGroups * kT;          // output columns of a work-group
+    static constexpr int kWaves = kT / P;               // search waves, and update waves
+    static constexpr int kThreads = 2 * 64 * kWaves;
+    static constexpr int NG = KW + kT - 1;              // columns of a group's windows
+    static constexpr int ND = (NG + 3) / 4;             // dwords of them
+    static constexpr int NB = kT * (kGroups - 1) + 4 * ND;   // bytes of a staged row
+    static constexpr int kRow = (NB + 15) / 16 * 16;
+    static constexpr int NL = (kRow + 63) / 64;         // byte loads of a whole row
+    static constexpr int NF = P == 1 ? (kRow + 127) / 128 : NL;   // of a wave's part of a row
+    static constexpr int CH = (ND + 1) / 2 * 4;         // columns of the first half of a row
+    static constexpr uint32_t kLds = kStage + 4 * kRow; // staged rows: [2 steps][row in, row out]
+
+    // Column i of a group adds 1 << shift(i) to word(i).
+    static constexpr int word(int i) { return P == 2 && (i == 2 || i >= KW); }
+    static constexpr int shift(int i)
+    {
+        if (i >= 3 && i < KW) return 0;
+        const int f = i < 3 ? i : 3 + i - KW;           // L0 L1 L2 R0 R1 R2
+        return P == 1 ? 8 + 4 * f : f < 2 ? 16 + 8 * f : 8 * (f - 2);
+    }
+
+    // flags of the group's bytes that lie in the window of output column w
+    static __device__ __forceinline__ uint32_t keep(int j, int w)
+    {
+        uint32_t m = 0x80808080u;
+        if (j == 0) m <<= 8 * w;
+        if (4 * j + 4 > KW) {                           // bytes w + KW and on are outside
+            const int n = w + KW - 4 * j;               // bytes of this dword inside
+            m = n >= 4 ? m : n <= 0 ? 0u : m & (0xffffffffu >> (32 - 8 * n));
+        }
+        return m;
+    }
+    // acc + number of the window's bytes >= m; nm = ~m in every byte. v_lerp
+    // gives (x + ~m + 1) >> 1 per byte, whose top bit is the carry: x >= m.
+    static __device__ __forceinline__ uint32_t count_ge(const uint32_t (&d)[ND], uint32_t nm, int w, uint32_t acc)
+    {
+#pragma unroll
+        for (int j = 0; j < ND; ++j)
+            acc = __builtin_popcount(__builtin_amdgcn_lerp(d[j], nm, 0x01010101u) & keep(j, w)) + acc;
+        return acc;
+    }
+    // window counts of output column w in N bins from address a on, st apart
+    template <int N>
+    static __device__ __forceinline__ void bins(int (&v)[N], uint32_t a, int st, int w)
+    {
+        uint32_t d[N][P];
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int q = 0; q < P; ++q) d[i][q] = *(const lds_u32*)(uintptr_t)(a + (uint32_t)(i * st) + 128u * q);
+        // all reads on their way before the first is waited for
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (P == 1) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[i] = (int)__builtin_amdgcn_udot8(d[i][0], 0x11100u << (4 * w), d[i][0] & 255u, false);
+        } else {
+            // three of L0 L1 (word 0, bytes 2 and 3), L2 R0 R1 R2 (word 1)
+            const uint32_t mA = 0x01010000u << (8 * w);
+            const uint32_t mB = w == 3 ? 0x01010100u : 0x01010101u >> (8 * (3 - w));
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                v[i] = (int)__builtin_amdgcn_udot4(d[i][P - 1], mB, __builtin_amdgcn_udot4(d[i][0], mA, d[i][0] & 0xffffu, false),
+                                                   false);
+        }
+    }
+    static __device__ __forceinline__ void read_row(uint32_t (&d)[ND], uint32_t loc)
+    {
+#pragma unroll
+        for (int j = 0; j + 4 <= ND; j += 4) {
+            const u32x4a4 v = *(const lds_u32x4a4*)(uintptr_t)(loc + 4 * j);
+            d[j] = v.x, d[j + 1] = v.y, d[j + 2] = v.z, d[j + 3] = v.w;
+        }
+#pragma unroll
+        for (int j = ND & ~3; j < ND; ++j) d[j] = *(const lds_u32*)(uintptr_t)(loc + 4 * j);
+    }
+
+    // Adds one (or removes: one = -1) for the row bytes of columns [C0, C1)
+    // of the group. With SYNC, the addresses are formed before a work-group
+    // barrier and the counters change after it.
+    template <int C0, int C1, bool SYNC>
+    static __device__ __forceinline__ void update(const uint32_t (&d)[ND], uint32_t g4, int one)
+    {
+        uint32_t a[C1 - C0];
+#pragma unroll
+        for (int i = C0; i < C1; ++i)
+            a[i - C0] = __builtin_amdgcn_perm(d[i / 4], word(i) ? g4 | 128u : g4, 0x0c0c0000u | ((4u + (i & 3)) << 8));
+        if (SYNC) __syncthreads();
+#pragma unroll
+        for (int i = C0; i < C1; ++i)
+            __hip_atomic_fetch_add((lds_u32*)(uintptr_t)(a[i - C0] + kPad), (uint32_t)one << shift(i), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+
+    // Rows [y0, y1) of the kCols columns from x0 on.
+    static __device__ __forceinline__ void strip(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
+                                                 int H, int W, long long pitch, int x0, int y0, int y1, int kh)
+    {
+        const int lane = (int)__lane_id();
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        for (uint32_t i = threadIdx.x * 16; i < kStage; i += kThreads * 16)
+            *(lds_u32x4*)(uintptr_t)i = u32x4{0, 0, 0, 0};
+        auto row = [&](int y) { return src + (long long)min(max(y, 0), H - 1) * pitch; };
+        if (wave < kWaves) search(row, dst, W, pitch, x0, y0, y1, kh, wave, lane);
+        else slide(row, W, x0, y0, y1, kh, wave - kWaves, lane);
+    }
+
+    // Next median of a lane: e = rank of the median - number of window values
+    // below bin m, am = address of bin m; both move to the median's bin.
+    static __device__ __forceinline__ void find(uint32_t& am, int& e, int w)
+    {
+        const int sg = e >> 31;
+        const int st = sg ? -256 : 256;
+        uint32_t a = am + (uint32_t)(sg & -256);
+        int n = e ^ sg;
+        uint32_t hi;
+        auto probe = [&](auto cnt) {
+            constexpr int N = decltype(cnt)::value;
+            int v[N];
+            bins<N>(v, a, st, w);
+            uint32_t lo = (uint32_t)n;
+            hi = 0;
+            int c = N, r = n;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                r -= v[i];
+                lo = min(lo, (uint32_t)r);
+                hi = max(hi, (uint32_t)r);
+                c += r >> 31;
+            }
+            a += (uint32_t)(st * c);
+            n = (int)lo;
+            return __any(c == N);
+        };
+        if (probe(std::integral_constant<int, 4>{}))
+            while (probe(std::integral_constant<int, 8>{})) {}
+        am = a;
+        e = sg ? (int)~hi : n;
+    }
+
+    template <class Row>
+    static __device__ __forceinline__ void search(const Row& row, unsigned char* __restrict__ dst, int W, long long pitch,
+                                                  int x0, int y0, int y1, int kh, int wave, int lane)
+    {
+        const int ry = kh / 2;
+        const uint32_t g4 = 4u * (uint32_t)(lane & (kGroups - 1));
+        const int w = P == 1 ? wave : 2 * wave + (lane >> 5);
+        const uint32_t vo = (uint32_t)(x0 + (int)g4 + w);
+        const bool inside = (int)vo < W;
+        uint32_t m;
+        {
+            const uint32_t xo = (uint32_t)min((int)vo, W - 1);
+            const uint32_t a = row(y0 - ry)[xo], b = row(y0)[xo], c = row(y0 + ry)[xo];
+            m = max(min(a, b), min(max(a, b), c));
+        }
+        uint32_t nge = 0, nm = ~(m * 0x01010101u);
+        for (int j = 0; j < kh; j += 4) {
+            __syncthreads();
+            for (int q = 0; q < 4 && j + q < kh; ++q) {
+                uint32_t d[ND];
+                read_row(d, kStage + q * kRow + g4);
+                nge = count_ge(d, nm, w, nge);
+            }
+            __syncthreads();
+        }
+        const int all = KW * kh;
+        int e = (all - 1) / 2 - (all - (int)nge);
+        uint32_t am = (m << 8) + g4 + kPad;
+        __syncthreads();
+        unsigned char* out = dst + (long long)y0 * pitch;
+        auto step = [&](int y, int par) {
+            find(am, e, w);
+            __syncthreads();
+            // the counters change from here to the next barrier; the median
+            // found and its rank in the next window do not depend on them
+            asm volatile("" : "+v"(am), "+v"(e));
+            m = ((am - kPad) >> 8) & 255u;
+            if (inside && y < y1) out[vo] = (unsigned char)m;
+            out += pitch;
+            uint32_t din[ND], dout[ND];
+            read_row(din, kStage + (2 * par) * kRow + g4);
+            read_row(dout, kStage + (2 * par + 1) * kRow + g4);
+            nm = ~__builtin_amdgcn_perm(m, m, 0u);
+            e = (int)(count_ge(din, nm, w, (uint32_t)e) - count_ge(dout, nm, w, 0));
+            asm volatile("" : "+v"(e));
+            __syncthreads();
+        };
+        for (int y = y0; y < y1; y += 2) {
+            step(y, 0);
+            step(y + 1, 1);
+        }
+    }
+
+    template <class Row>
+    static __device__ __forceinline__ void slide(const Row& row, int W, int x0, int y0, int y1, int kh, int wave, int lane)
+    {
+        const int rx = KW / 2, ry = kh / 2;
+        const uint32_t g4 = 4u * (uint32_t)(lane & (kGroups - 1));
+        const int sub = P == 1 ? 0 : lane >> 5;
+        auto gx_at = [&](int i) { return (uint32_t)min(max(x0 - rx + lane + i, 0), W - 1); };
+        // first window, four rows at a time
+        {
+            uint32_t gx[NL], b[P][NL];
+#pragma unroll
+            for (int i = 0; i < NL; ++i) gx[i] = gx_at(64 * i);
+            auto fetch = [&](int j) {
+#pragma unroll
+                for (int q = 0; q < P; ++q)
+#pragma unroll
+                    for (int i = 0; i < NL; ++i) b[q][i] = row(y0 - ry + j + wave * P + q)[gx[i]];
+            };
+            fetch(0);
+            for (int j = 0; j < kh; j += 4) {
+#pragma unroll
+                for (int q = 0; q < P; ++q)
+#pragma unroll
+                    for (int i = 0; i < NL; ++i)
+                        if (lane + 64 * i < kRow)
+                            *(lds_u8*)(uintptr_t)(kStage + (wave * P + q) * kRow + lane + 64 * i) = (uint8_t)b[q][i];
+                fetch(j + 4);
+                __syncthreads();
+                const int q = wave * P + sub;
+                if (j + q < kh) {
+                    uint32_t d[ND];
+                    read_row(d, kStage + q * kRow + g4);
+                    update<0, NG, false>(d, g4, 1);
+                }
+                __syncthreads();
+            }
+        }
+        // Steps: half (columns [0, CH) or [CH, NG)) of the row that enters or
+        // leaves is this wave's (P = 1) or half wave's (P = 2) to count.
+        const int half = P == 1 ? wave & 1 : wave;
+        const int leaves = P == 1 ? wave >> 1 : sub;
+        // and this part of one row to stage
+        const int frow = P == 1 ? wave >> 1 : wave, fx = P == 1 ? (wave & 1) * 64 * NF : 0;
+        const int yoff = frow ? -ry : ry + 1;
+        uint32_t gx[NF], buf[2][NF];
+#pragma unroll
+        for (int i = 0; i < NF; ++i) gx[i] = gx_at(fx + 64 * i);
+        auto fetch = [&](uint32_t (&b)[NF], int y) {
+            const unsigned char* p = row(y + yoff);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) b[i] = p[gx[i]];
+        };
+        auto put = [&](const uint32_t (&b)[NF], int par) {
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+                if (fx + lane + 64 * i < kRow)
+                    *(lds_u8*)(uintptr_t)(kStage + (2 * par + frow) * kRow + fx + lane + 64 * i) = (uint8_t)b[i];
+        };
+        fetch(buf[0], y0);
+        put(buf[0], 0);
+        fetch(buf[1], y0 + 1);
+        fetch(buf[0], y0 + 2);
+        __syncthreads();
+        auto step = [&](int y, int par, uint32_t (&b)[NF]) {
+            uint32_t d[ND];
+            read_row(d, kStage + (uint32_t)(2 * par + leaves) * kRow + g4);
+            put(b, par ^ 1);
+            fetch(b, y + 3);
+            const int one = leaves ? -1 : 1;
+            if (half) update<CH, NG, true>(d, g4, one);
+            else update<0, CH, true>(d, g4, one);
+            __syncthreads();
+        };
+        for (int y = y0; y < y1; y += 2) {
+            step(y, 0, buf[1]);
+            step(y + 1, 1, buf[0]);
+        }
+    }
+};
+
+template <int KW, int P>
+__global__ void __launch_bounds__(2 * 64 * kT / P)
+mf_hist_kernel(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst, int H, int W, long long pitch,
+               long long plane_stride, int ncol, int R, int kh)
+{
+    const int cb = (int)blockIdx.x % ncol, s = (int)blockIdx.x / ncol;
+    const long long po = (long long)blockIdx.y * plane_stride;   // plane = blockIdx.y
+    Hist<KW, P>::strip(src + po, dst + po, H, W, pitch, cb * Hist<KW, P>::kCols, s * R, min((s + 1) * R, H), kh);
+}
+
+// Rows of a block of the batched form: long enough that the first window
+// (KW rows) is a small part, short enough that images of a few hundred rows
+// still make several blocks.
+constexpr int kBatchRows = 64;
+
+template <int KW, int P>
+__global__ void __launch_bounds__(2 * 64 * kT / P)
+mf_hist_kernel_batched(const MfJob* __restrict__ jobs, int njobs, int nblocks)
+{
+    for (int b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        int lo = 0, hi = njobs - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (jobs[mid].block_begin <= b) lo = mid;
+            else hi = mid - 1;
+        }
+        const MfJob j = jobs[lo];
+        const int lb = b - j.block_begin;
+        const int y0 = lb / j.nbx * kBatchRows;
+        Hist<KW, P>::strip(j.src, j.dst, j.H, j.W, j.pitch, lb % j.nbx * Hist<KW, P>::kCols, y0,
+                           min(y0 + kBatchRows, j.H), KW);
+        __syncthreads();   // the next block reuses the LDS
+    }
+}
+
+template <int KW, int P, bool BATCHED>
+HistKernelInfo hist_kernel()
+{
+    typedef Hist<KW, P> Z;
+    const void* b = nullptr;
+    if constexpr (BATCHED) b = (const void*)mf_hist_kernel_batched<KW, P>;
+    return {(const void*)mf_hist_kernel<KW, P>, b, Z::kThreads, Z::kCols, kBatchRows, Z::kLds};
+}
+
+}  // namespace

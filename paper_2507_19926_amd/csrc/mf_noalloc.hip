@@ -19,6 +19,7 @@
 
 #include <mutex>
 
+#include "mf_hist.h"
 #include "mf_internal.h"
 
 int32_t mf_internal_fail(int32_t code, const char* msg);
@@ -130,7 +131,8 @@ extern "C" int32_t median_filter_batched_noalloc(const mf_image* imgs, int32_t n
             if (variant == MF_VARIANT_OBLIVIOUS) {
                 B.kern = packed ? kp16 : ku32;
             } else {
-                e = mf_da_batched(m.dtype, m.k, tw, th, group, &B.kern, &B.da, da_form);
+                e = da_form == kDaFormHist ? mf_hist_batched(m.k, &B.kern)
+                                           : mf_da_batched(m.dtype, m.k, tw, th, group, &B.kern, &B.da, da_form);
                 if (e != hipSuccess) return hip_fail(e, "data-aware batched kernel");
             }
         }

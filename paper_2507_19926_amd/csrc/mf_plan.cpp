@@ -20,6 +20,7 @@
 #include <tuple>
 #include <vector>
 
+#include "mf_hist.h"
 #include "mf_internal.h"
 
 // Shared with mf_api.cpp.
@@ -204,7 +205,8 @@ int32_t mf_plan_create(const mf_image* imgs, int32_t n, mf_plan* out)
             if (variant == MF_VARIANT_OBLIVIOUS) {
                 b.kern = packed ? kp16 : ku32;
             } else {
-                e = mf_da_batched(m.dtype, m.k, tw, th, group, &b.kern, &b.da, da_form);
+                e = da_form == kDaFormHist ? mf_hist_batched(m.k, &b.kern)
+                                           : mf_da_batched(m.dtype, m.k, tw, th, group, &b.kern, &b.da, da_form);
                 if (e != hipSuccess) {
                     plan_free(p);
                     return hip_fail(e, "data-aware batched kernel");
