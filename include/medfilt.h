@@ -81,7 +81,12 @@ typedef struct mf_options {
                          columns (small k), 3 = column-strip streaming form
                          (k = 3 only: root tile 1x1, each sorted column
                          shared by three windows, rows streamed through
-                         registers); 0 = library's                          */
+                         registers); data-aware: 1 = rounds per recursion
+                         level, 2 = rounds over the whole schedule, 3 =
+                         sliding histograms (MF_U8, k >= 13: root tile 1x1,
+                         the library's choice there; not among the
+                         configurations mf_list_configs enumerates, there
+                         is nothing in it to tune); 0 = library's          */
     int32_t rows;     /* oblivious: tile rows per wave; 0 = library's       */
 } mf_options;
 

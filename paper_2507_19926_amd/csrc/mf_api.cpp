@@ -713,6 +713,12 @@ int32_t median_filter_3d(const void* src, void* dst, int64_t D, int64_t H, int64
         }
         return MF_OK;
     }
+    // 8-bit volumes slide histograms for every k (256^3, uniform noise, against
+    // the schedule: k = 3 0.44 ms against 1.10, k = 5 0.45 against 2.14, k = 9
+    // 0.54 against 4.61)
+    if (mf_hist3_supports(dtype, k))
+        return hip_status(mf_hist3_launch(src, dst, (int)D, (int)H, (int)W, pitch_bytes, slice_bytes, k, st),
+                          "3-D sliding-histogram kernel launch");
     return hip_status(mf_da3_launch(src, dst, (int)D, (int)H, (int)W, pitch_bytes, slice_bytes, dtype, k, st),
                       "3-D kernel launch");
 }

@@ -24,3 +24,9 @@ hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plan
                           long long pitch, int kw, int kh, hipStream_t stream);
 // Batched kernel of the square k x k window (arguments: jobs, njobs, nblocks).
 hipError_t mf_hist_batched(int k, MfBatchedKernel* kern);
+
+// 3-D boxes, cubic k x k x k, of a D x H x W volume (rows pitch bytes apart,
+// slices slice bytes).
+bool mf_hist3_supports(int dtype, int k);
+hipError_t mf_hist3_launch(const void* src, void* dst, int D, int H, int W, long long pitch, long long slice, int k,
+                           hipStream_t stream);

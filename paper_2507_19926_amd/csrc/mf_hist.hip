@@ -9,10 +9,13 @@
 bool mf_hist_kernel_p1(int kw, HistKernelInfo* k);
 bool mf_hist_kernel_p2(int kw, HistKernelInfo* k);
 bool mf_hist_kernel_wide(int kw, HistKernelInfo* k);
+// 3-D boxes (mf_hist_box.hip)
+bool mf_hist_kernel_box(int k, HistKernelInfo* h);
 
 namespace {
 
 constexpr int kMaxDevices = 64;
+constexpr int kSlots = 4 * 38 + 16;   // slot_of() of windows, then boxes
 
 // All counts of the window fit the one-word layout: 4 bits for a column's
 // kh values, 8 for the kw - 3 shared columns'.
@@ -29,7 +32,7 @@ bool find(int kw, int kh, HistKernelInfo* k)
 // device and kernel.
 hipError_t allow_lds(const void* fn, int slot, int dev)
 {
-    static std::atomic<unsigned char> done[kMaxDevices][4 * 38];
+    static std::atomic<unsigned char> done[kMaxDevices][kSlots];
     if (done[dev][slot].load(std::memory_order_acquire)) return hipSuccess;
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e == hipSuccess) done[dev][slot].store(1, std::memory_order_release);
@@ -49,6 +52,26 @@ hipError_t device(int* dev, int* cus)
         count[*dev].store(*cus, std::memory_order_relaxed);
     }
     return hipSuccess;
+}
+
+// Rows of a strip, for `per_strip` work-groups side by side: a strip costs its
+// rows and `first` more for its first window; two work-groups run on each CU,
+// so of the launches of r rounds the one that fills them is the cheapest.
+int strip_rows(int H, long long per_strip, long long first, int cus)
+{
+    const long long slots = 2LL * cus;
+    long long best = -1;
+    int R = H;
+    for (int r = 1; r <= 8; ++r) {
+        long long n = r * slots / per_strip;
+        if (n < 1) n = 1;
+        if (n > H) n = H;
+        const int rows = (int)((H + n - 1) / n);
+        const long long strips = (H + rows - 1) / rows;
+        const long long cost = ((strips * per_strip + slots - 1) / slots) * (rows + first);
+        if (best < 0 || cost < best) best = cost, R = rows;
+    }
+    return R;
 }
 
 int slot_of(int kw, bool two, bool batched) { return (kw / 2) * 4 + (two ? 2 : 0) + (batched ? 1 : 0); }
@@ -72,29 +95,14 @@ hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plan
     e = allow_lds(k.planes, slot_of(kw, !(one_word(kw, kh) && kw <= 31), false), dev);
     if (e != hipSuccess) return e;
     const int ncol = (W + k.cols - 1) / k.cols;
-    // Strips of R rows: a strip costs its rows and, for its first window,
-    // about kh / 4 + 8 more; two work-groups run on each CU, so a launch of
-    // r full rounds of them is the cheapest for its r.
-    const long long slots = 2LL * cus, per_strip = (long long)ncol * planes;
-    const long long first = kh / 4 + 8;
-    long long best = -1;
-    int R = H;
-    for (int r = 1; r <= 8; ++r) {
-        long long n = r * slots / per_strip;
-        if (n < 1) n = 1;
-        if (n > H) n = H;
-        const int rows = (int)((H + n - 1) / n);
-        const long long strips = (H + rows - 1) / rows;
-        const long long cost = ((strips * per_strip + slots - 1) / slots) * (rows + first);
-        if (best < 0 || cost < best) best = cost, R = rows;
-    }
+    const int R = strip_rows(H, (long long)ncol * planes, kh / 4 + 8, cus);
     const int ns = (H + R - 1) / R;
     if ((long long)ncol * ns > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     for (int p0 = 0; p0 < planes; p0 += 65535) {     // grid rows are planes
         const int np = planes - p0 < 65535 ? planes - p0 : 65535;
         const unsigned char* s8 = (const unsigned char*)src + p0 * plane_stride;
         unsigned char* d8 = (unsigned char*)dst + p0 * plane_stride;
-        void* args[] = {&s8, &d8, &H, &W, &pitch, &plane_stride, (void*)&ncol, &R, &kh};
+        void* args[] = {&s8, &d8, &H, &W, &pitch, &plane_stride, (void*)&ncol, (void*)&R, &kh};
         e = hipLaunchKernel(k.planes, dim3((unsigned)(ncol * ns), np), dim3(k.threads), args, k.lds, stream);
         if (e != hipSuccess) return e;
     }
@@ -115,5 +123,34 @@ hipError_t mf_hist_batched(int k, MfBatchedKernel* kern)
     kern->lds = h.lds;
     kern->bw = h.cols;
     kern->bh = h.rows;
+    return hipSuccess;
+}
+
+bool mf_hist3_supports(int dtype, int k)
+{
+    HistKernelInfo h;
+    return dtype == MF_U8 && mf_hist_kernel_box(k, &h);
+}
+
+hipError_t mf_hist3_launch(const void* src, void* dst, int D, int H, int W, long long pitch, long long slice, int k,
+                           hipStream_t stream)
+{
+    HistKernelInfo h;
+    if (!mf_hist_kernel_box(k, &h)) return hipErrorInvalidValue;
+    int dev = 0, cus = 0;
+    hipError_t e = device(&dev, &cus);
+    if (e != hipSuccess) return e;
+    e = allow_lds(h.planes, 4 * 38 + k, dev);
+    if (e != hipSuccess) return e;
+    const int ncol = (W + h.cols - 1) / h.cols;
+    const int R = strip_rows(H, (long long)ncol * D, k * k / 4 + 8, cus);
+    const int ns = (H + R - 1) / R;
+    if ((long long)ncol * ns > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    for (int z0 = 0; z0 < D; z0 += 65535) {          // grid rows are slices
+        const int nz = D - z0 < 65535 ? D - z0 : 65535;
+        void* args[] = {&src, &dst, &D, &H, &W, &pitch, &slice, (void*)&ncol, (void*)&R, &z0};
+        e = hipLaunchKernel(h.planes, dim3((unsigned)(ncol * ns), nz), dim3(h.threads), args, h.lds, stream);
+        if (e != hipSuccess) return e;
+    }
     return hipSuccess;
 }

@@ -54,7 +54,7 @@ constexpr uint32_t kStage = kPad + kCounters + kPad;
 
 // Counter words of a group: P = 1: one, 64 groups to a work-group, bin v of
 // group g at 256 v + 4 g; P = 2: two, 32 groups, word p at 256 v + 128 p + 4 g.
-template <int KW, int P>
+template <int KW, int P, int Z = 1>
 struct Hist {
     static constexpr int kGroups = 64 / P;
     static constexpr int kCols = kGroups * kT;          // output columns of a work-group
@@ -67,7 +67,8 @@ struct Hist {
     static constexpr int NL = (kRow + 63) / 64;         // byte loads of a whole row
     static constexpr int NF = P == 1 ? (kRow + 127) / 128 : NL;   // of a wave's part of a row
     static constexpr int CH = (ND + 1) / 2 * 4;         // columns of the first half of a row
-    static constexpr uint32_t kLds = kStage + 4 * kRow; // staged rows: [2 steps][row in, row out]
+    // staged rows: [2 steps][in, out][Z slices]; the first window takes them four at a time
+    static constexpr uint32_t kLds = kStage + 4 * Z * kRow;
 
     // Column i of a group adds 1 << shift(i) to word(i).
     static constexpr int word(int i) { return P == 2 && (i == 2 || i >= KW); }
@@ -133,32 +134,42 @@ struct Hist {
         for (int j = ND & ~3; j < ND; ++j) d[j] = *(const lds_u32*)(uintptr_t)(loc + 4 * j);
     }
 
-    // Adds one (or removes: one = -1) for the row bytes of columns [C0, C1)
-    // of the group. With SYNC, the addresses are formed before a work-group
-    // barrier and the counters change after it.
-    template <int C0, int C1, bool SYNC>
-    static __device__ __forceinline__ void update(const uint32_t (&d)[ND], uint32_t g4, int one)
+    // Adds one (or removes: one = -1) for the bytes of columns [C0, C1) of
+    // the group in R rows. With SYNC, the addresses are formed before a
+    // work-group barrier and the counters change after it.
+    template <int C0, int C1, bool SYNC, int R>
+    static __device__ __forceinline__ void update(const uint32_t (&d)[R][ND], uint32_t g4, int one)
     {
-        uint32_t a[C1 - C0];
+        uint32_t a[R][C1 - C0];
 #pragma unroll
-        for (int i = C0; i < C1; ++i)
-            a[i - C0] = __builtin_amdgcn_perm(d[i / 4], word(i) ? g4 | 128u : g4, 0x0c0c0000u | ((4u + (i & 3)) << 8));
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = C0; i < C1; ++i)
+                a[r][i - C0] = __builtin_amdgcn_perm(d[r][i / 4], word(i) ? g4 | 128u : g4, 0x0c0c0000u | ((4u + (i & 3)) << 8));
         if (SYNC) __syncthreads();
 #pragma unroll
-        for (int i = C0; i < C1; ++i)
-            __hip_atomic_fetch_add((lds_u32*)(uintptr_t)(a[i - C0] + kPad), (uint32_t)one << shift(i), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = C0; i < C1; ++i)
+                __hip_atomic_fetch_add((lds_u32*)(uintptr_t)(a[r][i - C0] + kPad), (uint32_t)one << shift(i),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 
-    // Rows [y0, y1) of the kCols columns from x0 on.
+    // Rows [y0, y1) of the kCols columns from x0 on. For boxes (Z > 1) of
+    // slice z: src is the volume, slices `slice` bytes apart, D of them.
     static __device__ __forceinline__ void strip(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
-                                                 int H, int W, long long pitch, int x0, int y0, int y1, int kh)
+                                                 int H, int W, long long pitch, int x0, int y0, int y1, int kh,
+                                                 int D = 1, long long slice = 0, int z = 0)
     {
         const int lane = (int)__lane_id();
         const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
         for (uint32_t i = threadIdx.x * 16; i < kStage; i += kThreads * 16)
             *(lds_u32x4*)(uintptr_t)i = u32x4{0, 0, 0, 0};
-        auto row = [&](int y) { return src + (long long)min(max(y, 0), H - 1) * pitch; };
+        // row y of the q-th slice of the box
+        auto row = [&](int y, int q) {
+            const unsigned char* p = src + (long long)min(max(y, 0), H - 1) * pitch;
+            return Z == 1 ? p : p + (long long)min(max(z - Z / 2 + q, 0), D - 1) * slice;
+        };
         if (wave < kWaves) search(row, dst, W, pitch, x0, y0, y1, kh, wave, lane);
         else slide(row, W, x0, y0, y1, kh, wave - kWaves, lane);
     }
@@ -208,20 +219,20 @@ struct Hist {
         uint32_t m;
         {
             const uint32_t xo = (uint32_t)min((int)vo, W - 1);
-            const uint32_t a = row(y0 - ry)[xo], b = row(y0)[xo], c = row(y0 + ry)[xo];
+            const uint32_t a = row(y0 - ry, Z / 2)[xo], b = row(y0, Z / 2)[xo], c = row(y0 + ry, Z / 2)[xo];
             m = max(min(a, b), min(max(a, b), c));
         }
         uint32_t nge = 0, nm = ~(m * 0x01010101u);
-        for (int j = 0; j < kh; j += 4) {
+        for (int j = 0; j < kh * Z; j += 4) {
             __syncthreads();
-            for (int q = 0; q < 4 && j + q < kh; ++q) {
+            for (int q = 0; q < 4 && j + q < kh * Z; ++q) {
                 uint32_t d[ND];
                 read_row(d, kStage + q * kRow + g4);
                 nge = count_ge(d, nm, w, nge);
             }
             __syncthreads();
         }
-        const int all = KW * kh;
+        const int all = KW * kh * Z;
         int e = (all - 1) / 2 - (all - (int)nge);
         uint32_t am = (m << 8) + g4 + kPad;
         __syncthreads();
@@ -235,11 +246,17 @@ struct Hist {
             m = ((am - kPad) >> 8) & 255u;
             if (inside && y < y1) out[vo] = (unsigned char)m;
             out += pitch;
-            uint32_t din[ND], dout[ND];
-            read_row(din, kStage + (2 * par) * kRow + g4);
-            read_row(dout, kStage + (2 * par + 1) * kRow + g4);
             nm = ~__builtin_amdgcn_perm(m, m, 0u);
-            e = (int)(count_ge(din, nm, w, (uint32_t)e) - count_ge(dout, nm, w, 0));
+            uint32_t gone = 0;
+#pragma unroll
+            for (int q = 0; q < Z; ++q) {
+                uint32_t din[ND], dout[ND];
+                read_row(din, kStage + (uint32_t)((2 * par) * Z + q) * kRow + g4);
+                read_row(dout, kStage + (uint32_t)((2 * par + 1) * Z + q) * kRow + g4);
+                e = (int)count_ge(din, nm, w, (uint32_t)e);
+                gone = count_ge(dout, nm, w, gone);
+            }
+            e -= (int)gone;
             asm volatile("" : "+v"(e));
             __syncthreads();
         };
@@ -263,12 +280,14 @@ struct Hist {
             for (int i = 0; i < NL; ++i) gx[i] = gx_at(64 * i);
             auto fetch = [&](int j) {
 #pragma unroll
-                for (int q = 0; q < P; ++q)
+                for (int q = 0; q < P; ++q) {
+                    const int r = j + wave * P + q;
 #pragma unroll
-                    for (int i = 0; i < NL; ++i) b[q][i] = row(y0 - ry + j + wave * P + q)[gx[i]];
+                    for (int i = 0; i < NL; ++i) b[q][i] = row(y0 - ry + r / Z, r % Z)[gx[i]];
+                }
             };
             fetch(0);
-            for (int j = 0; j < kh; j += 4) {
+            for (int j = 0; j < kh * Z; j += 4) {
 #pragma unroll
                 for (int q = 0; q < P; ++q)
 #pragma unroll
@@ -278,9 +297,9 @@ struct Hist {
                 fetch(j + 4);
                 __syncthreads();
                 const int q = wave * P + sub;
-                if (j + q < kh) {
-                    uint32_t d[ND];
-                    read_row(d, kStage + q * kRow + g4);
+                if (j + q < kh * Z) {
+                    uint32_t d[1][ND];
+                    read_row(d[0], kStage + q * kRow + g4);
                     update<0, NG, false>(d, g4, 1);
                 }
                 __syncthreads();
@@ -293,28 +312,35 @@ struct Hist {
         // and this part of one row to stage
         const int frow = P == 1 ? wave >> 1 : wave, fx = P == 1 ? (wave & 1) * 64 * NF : 0;
         const int yoff = frow ? -ry : ry + 1;
-        uint32_t gx[NF], buf[2][NF];
+        uint32_t gx[NF], buf[2][Z][NF];
 #pragma unroll
         for (int i = 0; i < NF; ++i) gx[i] = gx_at(fx + 64 * i);
-        auto fetch = [&](uint32_t (&b)[NF], int y) {
-            const unsigned char* p = row(y + yoff);
+        auto fetch = [&](uint32_t (&b)[Z][NF], int y) {
 #pragma unroll
-            for (int i = 0; i < NF; ++i) b[i] = p[gx[i]];
+            for (int q = 0; q < Z; ++q) {
+                const unsigned char* p = row(y + yoff, q);
+#pragma unroll
+                for (int i = 0; i < NF; ++i) b[q][i] = p[gx[i]];
+            }
         };
-        auto put = [&](const uint32_t (&b)[NF], int par) {
+        auto put = [&](const uint32_t (&b)[Z][NF], int par) {
 #pragma unroll
-            for (int i = 0; i < NF; ++i)
-                if (fx + lane + 64 * i < kRow)
-                    *(lds_u8*)(uintptr_t)(kStage + (2 * par + frow) * kRow + fx + lane + 64 * i) = (uint8_t)b[i];
+            for (int q = 0; q < Z; ++q)
+#pragma unroll
+                for (int i = 0; i < NF; ++i)
+                    if (fx + lane + 64 * i < kRow)
+                        *(lds_u8*)(uintptr_t)(kStage + ((2 * par + frow) * Z + q) * kRow + fx + lane + 64 * i) =
+                            (uint8_t)b[q][i];
         };
         fetch(buf[0], y0);
         put(buf[0], 0);
         fetch(buf[1], y0 + 1);
         fetch(buf[0], y0 + 2);
         __syncthreads();
-        auto step = [&](int y, int par, uint32_t (&b)[NF]) {
-            uint32_t d[ND];
-            read_row(d, kStage + (uint32_t)(2 * par + leaves) * kRow + g4);
+        auto step = [&](int y, int par, uint32_t (&b)[Z][NF]) {
+            uint32_t d[Z][ND];
+#pragma unroll
+            for (int q = 0; q < Z; ++q) read_row(d[q], kStage + (uint32_t)((2 * par + leaves) * Z + q) * kRow + g4);
             put(b, par ^ 1);
             fetch(b, y + 3);
             const int one = leaves ? -1 : 1;
@@ -337,6 +363,17 @@ mf_hist_kernel(const unsigned char* __restrict__ src, unsigned char* __restrict_
     const int cb = (int)blockIdx.x % ncol, s = (int)blockIdx.x / ncol;
     const long long po = (long long)blockIdx.y * plane_stride;   // plane = blockIdx.y
     Hist<KW, P>::strip(src + po, dst + po, H, W, pitch, cb * Hist<KW, P>::kCols, s * R, min((s + 1) * R, H), kh);
+}
+
+// 3-D boxes, K x K x K: work-group row blockIdx.y is slice z0 + blockIdx.y.
+template <int K, int P>
+__global__ void __launch_bounds__(2 * 64 * kT / P)
+mf_hist3_kernel(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst, int D, int H, int W,
+                long long pitch, long long slice, int ncol, int R, int z0)
+{
+    typedef Hist<K, P, K> Box;
+    const int cb = (int)blockIdx.x % ncol, s = (int)blockIdx.x / ncol, z = z0 + (int)blockIdx.y;
+    Box::strip(src, dst + (long long)z * slice, H, W, pitch, cb * Box::kCols, s * R, min((s + 1) * R, H), K, D, slice, z);
 }
 
 // Rows of a block of the batched form: long enough that the first window
@@ -362,6 +399,13 @@ mf_hist_kernel_batched(const MfJob* __restrict__ jobs, int njobs, int nblocks)
                            min(y0 + kBatchRows, j.H), KW);
         __syncthreads();   // the next block reuses the LDS
     }
+}
+
+template <int K, int P>
+HistKernelInfo hist3_kernel()
+{
+    typedef Hist<K, P, K> Box;
+    return {(const void*)mf_hist3_kernel<K, P>, nullptr, Box::kThreads, Box::kCols, 0, Box::kLds};
 }
 
 template <int KW, int P, bool BATCHED>

@@ -1,7 +1,7 @@
 """Sliding-histogram form (8-bit data: square windows from k = 13 on, and
 rectangular windows without a network) against the CPU oracle, bit-exact: one
 and two counter words, edges of the column blocks and of the row strips,
-windows beyond the image, the fullest counters (constant and two-valued
+windows beyond the image, 3-D boxes, the fullest counters (constant and two-valued
 images), pitched rows, planes, the batched form and stream capture."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ import torch
 import oracle
 from paper_2507_19926_amd import _lib
 from paper_2507_19926_amd import workloads as wl
-from paper_2507_19926_amd.ops import BatchedPlan, median_filter, median_filter_rect
+from paper_2507_19926_amd.ops import BatchedPlan, median_filter, median_filter_3d, median_filter_rect
 
 pytestmark = pytest.mark.gpu
 
@@ -104,3 +104,13 @@ def test_batched_and_graph():
         g.replay()
         torch.cuda.synchronize()
         _check(np.roll(imgs[3], r + 1, axis=0), 25, 25, y.cpu().numpy())
+
+
+@pytest.mark.parametrize("k", [3, 5, 9, 15])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 17, 129), (9, 1, 23), (7, 8, 1), (5, 33, 260)])
+def test_boxes(k, shape):
+    D, H, W = shape
+    for seed in range(5):
+        vol = np.stack([list(_images(H, W, seed=z).values())[seed] for z in range(D)])
+        got = median_filter_3d(torch.from_numpy(vol).cuda(), k).cpu().numpy()
+        assert np.array_equal(got, oracle.median_filter_3d(vol, k)), seed
