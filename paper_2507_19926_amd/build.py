@@ -155,7 +155,8 @@ def build(jobs: int | None = None, verbose: bool = False, incremental: bool = Fa
             os.path.join(CSRC, "mf_autograd.hip"), os.path.join(CSRC, "mf_strip.hip"), os.path.join(CSRC, "mf_peaks.hip"),
             os.path.join(CSRC, "mf_noalloc.hip"), os.path.join(CSRC, "mf_hist.hip"),
             os.path.join(CSRC, "mf_hist_p1.hip"), os.path.join(CSRC, "mf_hist_p2.hip"),
-            os.path.join(CSRC, "mf_hist_wide.hip"), os.path.join(CSRC, "mf_hist_box.hip"), blob_cpp] + obl_srcs
+            os.path.join(CSRC, "mf_hist_wide.hip"), os.path.join(CSRC, "mf_hist_box.hip"),
+            os.path.join(CSRC, "mf_rank_u16.hip"), os.path.join(CSRC, "mf_rank_u32.hip"), blob_cpp] + obl_srcs
     objs = []
     jobs = jobs or min(16, os.cpu_count() or 4)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:

@@ -117,18 +117,40 @@ const OblEntry* find_obl(int k, int tw, int th, int nw, int form, int rows)
     return nullptr;
 }
 
-// Square windows of 8-bit data that run the sliding-histogram form: from
-// k = 13 on. Its time hardly depends on k but does on the data (the search
+// Square windows that run the sliding-histogram form: 8-bit data from k = 13
+// on. Its time hardly depends on k but does on the data (the search
 // walks from one row's median to the next, far on noise with a small window).
 // Per 30 MP RGB frame, smooth image / uniform noise against the network or
 // the schedule: k = 11 0.36 / 0.79 ms against 0.55 ms; k = 15 0.42 / 0.70
 // against 1.14; k = 17 0.60 / 1.04 against 1.42; k = 25 0.72 / 0.99 against
 // 10.4; k = 75 1.41 / 1.43 against 39.8.
-bool hist_is_faster(int32_t dtype, int32_t k) { return k >= 13 && mf_hist_supports(dtype, k, k); }
+// 16- and 32-bit data rank the values first, so their line lies where the
+// networks end or slow down (4096^2, uniform 16-bit and normal float32 data):
+// 16-bit k = 21 0.70 ms against the network's 0.68, k = 25 0.68 against 3.16
+// (schedule), k = 75 1.12 against 12.8; float32 k = 19 0.93 against 0.96, k = 21 0.96 against 1.84, k = 25 0.93
+// against 5.47, k = 75 1.53 against 24.3.
+bool hist_is_faster(int32_t dtype, int32_t k)
+{
+    const int32_t from = dtype == MF_U8 ? 13 : dtype == MF_U16 ? 23 : 21;
+    return k >= from && mf_hist_supports(dtype, k, k);
+}
 
-// Resolve (dtype, k, opt) to a variant and root tile. Host only.
+// Calls of fewer pixels keep 16- and 32-bit data on the schedules: a ranked
+// region takes its 40-120 us (sort, first window, rows) however few there are,
+// the schedules' time falls with the pixels (us, ranked / schedule, one plane:
+// 16-bit 320^2 k = 23 44 / 33, 384^2 43 / 50, 512^2 43 / 58; float32 320^2
+// 66 / 52, 384^2 66 / 73, 512^2 66 / 94; k = 75 16-bit 256^2 78 / 67, 384^2
+// 78 / 177).
+bool too_small_to_rank(int32_t dtype, int64_t planes, int64_t H, int64_t W)
+{
+    return dtype != MF_U8 && H * W < (1 << 17) && planes * H * W < (1 << 17);
+}
+
+// Resolve (dtype, k, opt) to a variant and root tile; small: of a call that
+// is too_small_to_rank(). Host only.
 int32_t resolve(int32_t dtype, int32_t k, const mf_options* opt, int32_t* variant, int32_t* tw,
-                int32_t* th, const OblEntry** obl, int32_t* group = nullptr, int32_t* da_form = nullptr)
+                int32_t* th, const OblEntry** obl, int32_t* group = nullptr, int32_t* da_form = nullptr,
+                bool small = false)
 {
     mf_options o = {};
     if (opt) o = *opt;
@@ -147,7 +169,7 @@ int32_t resolve(int32_t dtype, int32_t k, const mf_options* opt, int32_t* varian
     // measured choice for this (value class, k), when nothing was requested
     if (o.rows < 0) return fail(MF_ERR_CONFIG, "rows %d must be >= 0", o.rows);
     if (o.variant == MF_VARIANT_AUTO && !o.tile_w && !o.tile_h && !o.group && !o.form && !o.rows) {
-        if (hist_is_faster(dtype, k)) {
+        if (hist_is_faster(dtype, k) && !small) {
             *variant = MF_VARIANT_DATA_AWARE;
             *tw = *th = 1;
             if (group) *group = 1;
@@ -199,9 +221,9 @@ int32_t resolve(int32_t dtype, int32_t k, const mf_options* opt, int32_t* varian
     int dtw = o.tile_w, dth = o.tile_h, dg = o.group, df = o.form;
     if (df == kDaFormHist) {
         if (o.variant != MF_VARIANT_DATA_AWARE || dtw > 1 || dth > 1 || dg > 1 || o.rows ||
-            !mf_hist_supports(dtype, k, k) || k < 13)
-            return fail(MF_ERR_CONFIG, "form 3 is the oblivious column-strip form (k = 3) or the data-aware "
-                                       "sliding-histogram form (8-bit data, k >= 13, root tile 1x1)");
+            !hist_is_faster(dtype, k))
+            return fail(MF_ERR_CONFIG, "form 3 is the oblivious column-strip form (k = 3) or, where it is the "
+                                       "library's choice, the data-aware sliding-histogram form (root tile 1x1)");
         *variant = MF_VARIANT_DATA_AWARE;
         *tw = *th = 1;
         if (group) *group = 1;
@@ -259,11 +281,25 @@ int32_t mf_internal_validate(const void* src, const void* dst, int64_t H, int64_
 
 int32_t mf_internal_fail(int32_t code, const char* msg) { return fail(code, "%s", msg); }
 
+// Whether the images of a batch that would be ranked are together too few.
+bool mf_internal_small_batch(const mf_image* imgs, int32_t n)
+{
+    int64_t px = 0;
+    for (int i = 0; i < n; ++i)
+        if (imgs[i].dtype != MF_U8 && hist_is_faster(imgs[i].dtype, imgs[i].k)) {
+            if (!too_small_to_rank(imgs[i].dtype, 1, imgs[i].H, imgs[i].W)) return false;
+            px += imgs[i].H * imgs[i].W;
+            if (!too_small_to_rank(imgs[i].dtype, 1, 1, px)) return false;
+        }
+    return true;
+}
+
 int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t* tw, int32_t* th,
-                            int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form)
+                            int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form,
+                            bool small)
 {
     const OblEntry* e = nullptr;
-    int32_t rc = resolve(dtype, k, nullptr, variant, tw, th, &e, group, da_form);
+    int32_t rc = resolve(dtype, k, nullptr, variant, tw, th, &e, group, da_form, small && dtype != MF_U8);
     if (rc) return rc;
     // the column-strip form has no batched kernel: plans use k's default
     // network
@@ -374,10 +410,11 @@ int32_t median_filter_rect(const void* src, void* dst, int64_t planes, int64_t p
         return fail(MF_ERR_CONFIG, "no oblivious network compiled for the %dx%d window", kw, kh);
     if (!mf_da_supports(dtype, kw, 0, 0, 0, kh))
         return fail(MF_ERR_CONFIG, "no data-aware schedule for the %dx%d window", kw, kh);
-    // 8-bit data without a network: sliding histograms instead of the schedule
-    if (variant == MF_VARIANT_AUTO && mf_hist_supports(dtype, kw, kh))
-        return hip_status(mf_hist_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, kw,
-                                         kh, (hipStream_t)stream),
+    // without a network: sliding histograms instead of the schedule (30 MP RGB
+    // 8-bit frame: 21x13 0.45 ms against 9.9, 31x29 0.87 against 22 on noise)
+    if (variant == MF_VARIANT_AUTO && mf_hist_supports(dtype, kw, kh) && !too_small_to_rank(dtype, planes, H, W))
+        return hip_status(mf_hist_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, dtype,
+                                         kw, kh, (hipStream_t)stream),
                           "sliding-histogram kernel launch");
     return hip_status(mf_da_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, dtype, kw,
                                    0, 0, 0, (hipStream_t)stream, kh),
@@ -437,7 +474,7 @@ int32_t median_filter_planes(const void* src, void* dst, int64_t planes, int64_t
                                          st);
     int32_t variant = 0, tw = 0, th = 0, group = 0, da_form = 0;
     const OblEntry* e = nullptr;
-    rc = resolve(dtype, k, opt, &variant, &tw, &th, &e, &group, &da_form);
+    rc = resolve(dtype, k, opt, &variant, &tw, &th, &e, &group, &da_form, too_small_to_rank(dtype, planes, H, W));
     if (rc) return rc;
     if (variant == MF_VARIANT_OBLIVIOUS) {
         mf_launch_fn fn = (dtype == MF_U8 || dtype == MF_U16) ? e->p16 : e->u32;
@@ -445,8 +482,8 @@ int32_t median_filter_planes(const void* src, void* dst, int64_t planes, int64_t
                           "oblivious kernel launch");
     }
     if (da_form == kDaFormHist)
-        return hip_status(mf_hist_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, k, k,
-                                         st),
+        return hip_status(mf_hist_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, dtype,
+                                         k, k, st),
                           "sliding-histogram kernel launch");
     return hip_status(mf_da_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, dtype, k,
                                    tw, th, group, st, 0, da_form),

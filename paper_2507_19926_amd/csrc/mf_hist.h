@@ -1,4 +1,6 @@
-// Sliding-histogram form of the median filter for 8-bit planes (mf_hist.hip).
+// Sliding-histogram forms of the median filter (mf_hist.hip): 8-bit planes
+// (mf_hist_kernel.h), and 16- and 32-bit planes whose values are replaced by
+// buckets of their ranks (mf_rank_kernel.h).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -21,9 +23,9 @@ struct HistKernelInfo {
 bool mf_hist_supports(int dtype, int kw, int kh);
 // `planes` planes of H x W, plane p at src/dst + p * plane_stride bytes.
 hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plane_stride, int H, int W,
-                          long long pitch, int kw, int kh, hipStream_t stream);
+                          long long pitch, int dtype, int kw, int kh, hipStream_t stream);
 // Batched kernel of the square k x k window (arguments: jobs, njobs, nblocks).
-hipError_t mf_hist_batched(int k, MfBatchedKernel* kern);
+hipError_t mf_hist_batched(int dtype, int k, MfBatchedKernel* kern);
 
 // 3-D boxes, cubic k x k x k, of a D x H x W volume (rows pitch bytes apart,
 // slices slice bytes).

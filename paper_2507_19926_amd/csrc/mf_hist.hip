@@ -1,5 +1,5 @@
-// Sliding-histogram form: choice of kernel and launch (the kernels are
-// described in mf_hist_kernel.h).
+// Sliding-histogram forms: choice of kernel and launch (the kernels are
+// described in mf_hist_kernel.h and mf_rank_kernel.h).
 #include <atomic>
 
 #include "mf_hist_kernel.h"
@@ -9,21 +9,29 @@
 bool mf_hist_kernel_p1(int kw, HistKernelInfo* k);
 bool mf_hist_kernel_p2(int kw, HistKernelInfo* k);
 bool mf_hist_kernel_wide(int kw, HistKernelInfo* k);
+// 16- and 32-bit data (mf_rank_u16.hip, mf_rank_u32.hip)
+bool mf_rank_kernel_u16(int kw, HistKernelInfo* k);
+bool mf_rank_kernel_u32(int kw, HistKernelInfo* k);
 // 3-D boxes (mf_hist_box.hip)
 bool mf_hist_kernel_box(int k, HistKernelInfo* h);
 
 namespace {
 
 constexpr int kMaxDevices = 64;
-constexpr int kSlots = 4 * 38 + 16;   // slot_of() of windows, then boxes
+constexpr int kSlots = 8 * 38 + 16;   // slot_of() of windows, then boxes
 
 // All counts of the window fit the one-word layout: 4 bits for a column's
 // kh values, 8 for the kw - 3 shared columns'.
 bool one_word(int kw, int kh) { return kh <= 15 && kh * (kw - 3) <= 255; }
 
-bool find(int kw, int kh, HistKernelInfo* k)
+bool find(int dtype, int kw, int kh, HistKernelInfo* k)
 {
-    if (kw < 3 || kw % 2 == 0 || kh < 1 || kh > 255) return false;
+    if (kw < 3 || kw % 2 == 0 || kh < 1) return false;
+    if (dtype != MF_U8) {
+        if (kw <= 31 ? kh > 31 : kh != kw) return false;
+        return dtype == MF_U16 ? mf_rank_kernel_u16(kw, k) : mf_rank_kernel_u32(kw, k);
+    }
+    if (kh > 255) return false;
     if (one_word(kw, kh) && kw <= 31) return mf_hist_kernel_p1(kw, k);
     return kw <= 31 ? mf_hist_kernel_p2(kw, k) : mf_hist_kernel_wide(kw, k);
 }
@@ -74,49 +82,75 @@ int strip_rows(int H, long long per_strip, long long first, int cus)
     return R;
 }
 
-int slot_of(int kw, bool two, bool batched) { return (kw / 2) * 4 + (two ? 2 : 0) + (batched ? 1 : 0); }
+// Output rows of a ranked region, by the measured clocks of its parts (uniform
+// noise, k = 25..75): 5 (16-bit) or 10 (32-bit) for a value of the footprint,
+// loaded, sorted and listed, 300 for a row of the first window, 1600 for an
+// output row slid, searched and walked; one region to a CU.
+int rank_rows(int H, long long per_strip, int fw, int kh, bool wide, int cus)
+{
+    long long best = -1;
+    int R = 64;
+    for (int r = 64; r >= 8; r -= 8) {
+        const long long regions = (H + r - 1) / r * per_strip;
+        const int used = r < H ? r : H;
+        const long long cost = (regions + cus - 1) / cus *
+                               ((wide ? 10LL : 5LL) * fw * (used + kh - 1) + 300LL * kh + 1600LL * used + 5000);
+        if (best < 0 || cost < best) best = cost, R = r;
+    }
+    return R;
+}
+
+// one number for each kernel of a window
+int slot_of(int dtype, int kw, int kh, bool batched)
+{
+    const int kind = dtype == MF_U16 ? 2 : dtype != MF_U8 ? 3 : one_word(kw, kh) && kw <= 31 ? 0 : 1;
+    return (kw / 2) * 8 + kind * 2 + (batched ? 1 : 0);
+}
 
 }  // namespace
 
 bool mf_hist_supports(int dtype, int kw, int kh)
 {
     HistKernelInfo k;
-    return dtype == MF_U8 && find(kw, kh, &k);
+    return find(dtype, kw, kh, &k);
 }
 
 hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plane_stride, int H, int W,
-                          long long pitch, int kw, int kh, hipStream_t stream)
+                          long long pitch, int dtype, int kw, int kh, hipStream_t stream)
 {
     HistKernelInfo k;
-    if (!find(kw, kh, &k)) return hipErrorInvalidValue;
+    if (!find(dtype, kw, kh, &k)) return hipErrorInvalidValue;
     int dev = 0, cus = 0;
     hipError_t e = device(&dev, &cus);
     if (e != hipSuccess) return e;
-    e = allow_lds(k.planes, slot_of(kw, !(one_word(kw, kh) && kw <= 31), false), dev);
+    e = allow_lds(k.planes, slot_of(dtype, kw, kh, false), dev);
     if (e != hipSuccess) return e;
     const int ncol = (W + k.cols - 1) / k.cols;
-    const int R = strip_rows(H, (long long)ncol * planes, kh / 4 + 8, cus);
+    const bool rank = dtype != MF_U8;
+    const int R = rank ? rank_rows(H, (long long)ncol * planes, k.cols + kw - 1, kh, dtype != MF_U16, cus)
+                       : strip_rows(H, (long long)ncol * planes, kh / 4 + 8, cus);
+    int is_float = dtype == MF_F32;
     const int ns = (H + R - 1) / R;
     if ((long long)ncol * ns > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     for (int p0 = 0; p0 < planes; p0 += 65535) {     // grid rows are planes
         const int np = planes - p0 < 65535 ? planes - p0 : 65535;
         const unsigned char* s8 = (const unsigned char*)src + p0 * plane_stride;
         unsigned char* d8 = (unsigned char*)dst + p0 * plane_stride;
-        void* args[] = {&s8, &d8, &H, &W, &pitch, &plane_stride, (void*)&ncol, (void*)&R, &kh};
+        void* args[] = {&s8, &d8, &H, &W, &pitch, &plane_stride, (void*)&ncol, (void*)&R, &kh, &is_float};   // is_float: ranked kernels
         e = hipLaunchKernel(k.planes, dim3((unsigned)(ncol * ns), np), dim3(k.threads), args, k.lds, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-hipError_t mf_hist_batched(int k, MfBatchedKernel* kern)
+hipError_t mf_hist_batched(int dtype, int k, MfBatchedKernel* kern)
 {
     HistKernelInfo h;
-    if (!find(k, k, &h) || !h.batched) return hipErrorInvalidValue;
+    if (!find(dtype, k, k, &h) || !h.batched) return hipErrorInvalidValue;
     int dev = 0, cus = 0;
     hipError_t e = device(&dev, &cus);
     if (e != hipSuccess) return e;
-    e = allow_lds(h.batched, slot_of(k, !one_word(k, k), true), dev);
+    e = allow_lds(h.batched, slot_of(dtype, k, k, true), dev);
     if (e != hipSuccess) return e;
     kern->fn = h.batched;
     kern->threads = h.threads;
@@ -140,7 +174,7 @@ hipError_t mf_hist3_launch(const void* src, void* dst, int D, int H, int W, long
     int dev = 0, cus = 0;
     hipError_t e = device(&dev, &cus);
     if (e != hipSuccess) return e;
-    e = allow_lds(h.planes, 4 * 38 + k, dev);
+    e = allow_lds(h.planes, 8 * 38 + k, dev);
     if (e != hipSuccess) return e;
     const int ncol = (W + h.cols - 1) / h.cols;
     const int R = strip_rows(H, (long long)ncol * D, k * k / 4 + 8, cus);

@@ -176,7 +176,8 @@ struct Hist {
 
     // Next median of a lane: e = rank of the median - number of window values
     // below bin m, am = address of bin m; both move to the median's bin.
-    static __device__ __forceinline__ void find(uint32_t& am, int& e, int w)
+    // Returns the number of window values of that bin that rank above.
+    static __device__ __forceinline__ int find(uint32_t& am, int& e, int w)
     {
         const int sg = e >> 31;
         const int st = sg ? -256 : 256;
@@ -205,6 +206,7 @@ struct Hist {
             while (probe(std::integral_constant<int, 8>{})) {}
         am = a;
         e = sg ? (int)~hi : n;
+        return sg ? n : (int)~hi;
     }
 
     template <class Row>

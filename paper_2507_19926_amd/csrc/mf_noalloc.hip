@@ -24,7 +24,9 @@
 
 int32_t mf_internal_fail(int32_t code, const char* msg);
 int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t* tw, int32_t* th,
-                            int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form);
+                            int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form,
+                            bool small);
+bool mf_internal_small_batch(const mf_image* imgs, int32_t n);
 int32_t mf_internal_check_images(const mf_image* imgs, int32_t n);
 void mf_internal_batched_grids(int n, const MfBatchedKernel* kern, const long long* blocks, const int* k,
                                 unsigned* grid);
@@ -101,12 +103,13 @@ extern "C" int32_t median_filter_batched_noalloc(const mf_image* imgs, int32_t n
     }
     MfJob* const base = g_ptr[dev];
     // group the images by kernel, in first-appearance order
+    const bool small = mf_internal_small_batch(imgs, n);
     int nb = 0;
     for (int i = 0; i < n; ++i) {
         const mf_image& m = imgs[i];
         int32_t variant = 0, tw = 0, th = 0, group = 0, da_form = 0;
         MfBatchedKernel kp16 = {}, ku32 = {};
-        rc = mf_internal_resolve(m.dtype, m.k, &variant, &tw, &th, &group, &kp16, &ku32, &da_form);
+        rc = mf_internal_resolve(m.dtype, m.k, &variant, &tw, &th, &group, &kp16, &ku32, &da_form, small);
         if (rc) return rc;
         // kernel class: the oblivious kernels serve 8- and 16-bit data alike;
         // the data-aware kernels differ for 8-bit data (byte elements),
@@ -131,7 +134,7 @@ extern "C" int32_t median_filter_batched_noalloc(const mf_image* imgs, int32_t n
             if (variant == MF_VARIANT_OBLIVIOUS) {
                 B.kern = packed ? kp16 : ku32;
             } else {
-                e = da_form == kDaFormHist ? mf_hist_batched(m.k, &B.kern)
+                e = da_form == kDaFormHist ? mf_hist_batched(m.dtype, m.k, &B.kern)
                                            : mf_da_batched(m.dtype, m.k, tw, th, group, &B.kern, &B.da, da_form);
                 if (e != hipSuccess) return hip_fail(e, "data-aware batched kernel");
             }

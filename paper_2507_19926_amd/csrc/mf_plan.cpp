@@ -28,7 +28,9 @@ int32_t mf_internal_validate(const void* src, const void* dst, int64_t H, int64_
                              int32_t dtype, int32_t k, int32_t border);
 int32_t mf_internal_fail(int32_t code, const char* msg);
 int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t* tw, int32_t* th,
-                            int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form);
+                            int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form,
+                            bool small);
+bool mf_internal_small_batch(const mf_image* imgs, int32_t n);
 
 namespace {
 
@@ -175,12 +177,13 @@ int32_t mf_plan_create(const mf_image* imgs, int32_t n, mf_plan* out)
         return hip_fail(e, "hipGetDevice");
     }
     // bucket by kernel
+    const bool small = mf_internal_small_batch(imgs, n);
     std::map<std::tuple<int, int, int, int, int>, int> index;
     for (int i = 0; i < n; ++i) {
         const mf_image& m = imgs[i];
         int32_t variant = 0, tw = 0, th = 0, group = 0, da_form = 0;
         MfBatchedKernel kp16 = {}, ku32 = {};
-        rc = mf_internal_resolve(m.dtype, m.k, &variant, &tw, &th, &group, &kp16, &ku32, &da_form);
+        rc = mf_internal_resolve(m.dtype, m.k, &variant, &tw, &th, &group, &kp16, &ku32, &da_form, small);
         if (rc) {
             plan_free(p);
             return rc;
@@ -205,7 +208,7 @@ int32_t mf_plan_create(const mf_image* imgs, int32_t n, mf_plan* out)
             if (variant == MF_VARIANT_OBLIVIOUS) {
                 b.kern = packed ? kp16 : ku32;
             } else {
-                e = da_form == kDaFormHist ? mf_hist_batched(m.k, &b.kern)
+                e = da_form == kDaFormHist ? mf_hist_batched(m.dtype, m.k, &b.kern)
                                            : mf_da_batched(m.dtype, m.k, tw, th, group, &b.kern, &b.da, da_form);
                 if (e != hipSuccess) {
                     plan_free(p);

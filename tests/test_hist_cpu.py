@@ -7,6 +7,10 @@ import pytest
 from paper_2507_19926_amd import _lib
 
 
+# first square window of the form, by type
+FIRST = {_lib.MF_U8: 13, _lib.MF_U16: 23, _lib.MF_U32: 21, _lib.MF_F32: 21}
+
+
 def _resolve(dtype, k, *opt):
     o, r = _lib.options(*opt), _lib.mf_options()
     _lib.check(_lib.lib().mf_query_options(dtype, k, ctypes.byref(o), ctypes.byref(r)))
@@ -16,20 +20,20 @@ def _resolve(dtype, k, *opt):
 @pytest.mark.parametrize("k", list(range(3, 76, 2)))
 def test_choice_by_type_and_window(k):
     hist = (_lib.MF_VARIANT_DATA_AWARE, 1, 1, 1, 3, 0)
-    assert (_lib.query_options(_lib.MF_U8, k) == hist) == (k >= 13)
-    for dtype in (_lib.MF_U16, _lib.MF_U32, _lib.MF_F32):
-        assert _lib.query_options(dtype, k) != hist
+    for dtype, first in FIRST.items():
+        assert (_lib.query_options(dtype, k) == hist) == (k >= first)
 
 
 def test_reported_configuration_resolves_to_itself():
-    for k in (13, 17, 75):
-        v, tw, th, g, f, r = _lib.query_options(_lib.MF_U8, k)
-        assert _resolve(_lib.MF_U8, k, v, (tw, th), g, f, r) == (v, tw, th, g, f, r)
+    for dtype, first in FIRST.items():
+        for k in (first, 75):
+            v, tw, th, g, f, r = _lib.query_options(dtype, k)
+            assert _resolve(dtype, k, v, (tw, th), g, f, r) == (v, tw, th, g, f, r)
 
 
 def test_refused():
     for dtype, k, o in ((_lib.MF_U8, 11, (_lib.MF_VARIANT_DATA_AWARE, None, 0, 3)),
-                        (_lib.MF_U16, 25, (_lib.MF_VARIANT_DATA_AWARE, None, 0, 3)),
+                        (_lib.MF_U16, 17, (_lib.MF_VARIANT_DATA_AWARE, None, 0, 3)),
                         (_lib.MF_U8, 25, (_lib.MF_VARIANT_AUTO, None, 0, 3)),
                         (_lib.MF_U8, 17, (_lib.MF_VARIANT_OBLIVIOUS, None, 0, 3)),
                         (_lib.MF_U8, 25, (_lib.MF_VARIANT_DATA_AWARE, (2, 1), 0, 3)),
