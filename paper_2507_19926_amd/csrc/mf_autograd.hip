@@ -19,52 +19,148 @@ namespace {
 
 constexpr int kBX = 64, kBY = 4;           // output block of one work-group
 constexpr int kThreads = kBX * kBY;
+constexpr int kRows = 4;                   // output rows of a lane (argmedian)
+constexpr int kAY = kBY * kRows;           // block rows of the argmedian and of the bit maps
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
 }  // namespace
 
-// One work-group: a 64 x 4 block of one plane. The window union
-// ((64 + k - 1) x (4 + k - 1) values) is staged in LDS as float bits.
+// One work-group: a 64 x 16 block of one plane, four output rows to a lane.
+// The window union ((64 + k - 1) x (16 + k - 1) values) is staged in LDS as
+// float bits; a row of it that lies in several of the lane's windows is read
+// once and compared with each of their medians. The match of a whole row is
+// one bit per lane, so a comparison is one VALU instruction (its or is
+// scalar); the row found is then read again, from its end, for the column.
+//
+// Bound: VALU, 1.5 k * k instructions per output. 32x3x512x512: k = 7 0.31 ms with
+// one row to a lane (k * k reads, compares and selects), 0.14 now; k = 15 0.75
+// and 0.37. (A scalar or of the compares' masks instead of v_min3: k = 7 0.15,
+// k = 15 1.31, the masks outgrow the scalar registers.)
+template <int K>
 __global__ void __launch_bounds__(kThreads)
 mf_argmedian_kernel(const uint32_t* __restrict__ src, const uint32_t* __restrict__ med,
-                    int32_t* __restrict__ idx, int H, int W, int k, int nbx, int nby)
+                    int32_t* __restrict__ idx, int H, int W, int k_rt, int nbx, int nby)
 {
     extern __shared__ uint32_t tile[];
+    const int k = K ? K : k_rt;
     const int plane = blockIdx.x / (nbx * nby);
     const int b = blockIdx.x - plane * nbx * nby;
     const int by = b / nbx, bx = b - by * nbx;
     const int r = (k - 1) / 2;
     const long long base = (long long)plane * H * W;
-    const int X0 = bx * kBX, Y0 = by * kBY;
-    const int lw = kBX + 2 * r, lh = kBY + 2 * r;
+    const int X0 = bx * kBX, Y0 = by * kAY;
+    const int lw = kBX + 2 * r, lh = kAY + 2 * r;
     for (int i = threadIdx.x; i < lw * lh; i += kThreads) {
         const int y = i / lw, x = i - y * lw;
         const int gy = clampi(Y0 - r + y, 0, H - 1), gx = clampi(X0 - r + x, 0, W - 1);
-        tile[y * lw + x] = src[base + (long long)gy * W + gx];
+        tile[i] = src[base + (long long)gy * W + gx];
+    }
+    const int tx = threadIdx.x % kBX, ty = threadIdx.x / kBX * kRows;
+    const int x = X0 + tx;
+    uint32_t m[kRows];
+    int row[kRows];            // first row of the window that holds the median
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+        const int y = min(Y0 + ty + j, H - 1);
+        m[j] = med[base + (long long)y * W + min(x, W - 1)];
+        row[j] = -1;
+    }
+    __syncthreads();
+    for (int t = 0; t < k + kRows - 1; ++t) {
+        const uint32_t* p = tile + (ty + t) * lw + tx;
+        uint32_t off[kRows];   // 0 where the row holds the median
+#pragma unroll
+        for (int j = 0; j < kRows; ++j) off[j] = p[0] ^ m[j];
+#pragma unroll 4
+        for (int dx = 1; dx < k; dx += 2) {
+            const uint32_t v = p[dx], u = p[dx + 1];
+#pragma unroll
+            for (int j = 0; j < kRows; ++j) off[j] = min(off[j], min(v ^ m[j], u ^ m[j]));
+        }
+#pragma unroll
+        for (int j = 0; j < kRows; ++j)
+            if (t >= j && t - j < k) row[j] = off[j] == 0 && row[j] < 0 ? t - j : row[j];
+    }
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+        const int y = Y0 + ty + j;
+        if (y >= H || x >= W) continue;
+        const uint32_t* p = tile + (ty + j + max(row[j], 0)) * lw + tx;
+        int col = 0;
+#pragma unroll 8
+        for (int dx = k - 1; dx >= 0; --dx) col = p[dx] == m[j] ? dx : col;
+        idx[base + (long long)y * W + x] =
+            row[j] < 0 ? -1 : clampi(y - r + row[j], 0, H - 1) * W + clampi(x - r + col, 0, W - 1);
+    }
+}
+
+// Backward, windows of up to 31: a work-group takes 64 x ROWS input pixels. An
+// output pixel p that names one of them, q, sets in q's bit map the bit of
+// its place in q's window (rows of RB bits: 8, 16 or 32 for k up to 7, 15 and
+// 31); bits are set by LDS or, in any order. Every q then adds grad_out over
+// its set bits from the lowest on, which is ascending p. Work per pixel is one
+// or and one addition per naming instead of k * k comparisons.
+//
+// Bound: instruction issue and LDS latency of the bit loops (a wave runs as
+// long as its most named pixel), from k = 17 on the LDS the maps leave for
+// other work-groups. 32x3x512x512, comparing k * k neighbours and now: k = 7
+// 0.35 and 0.18 ms, k = 15 0.91 and 0.36, k = 31 3.8 and 0.99.
+template <int RB, int ROWS, int THREADS>
+__global__ void __launch_bounds__(THREADS)
+mf_grad_bits_kernel(const float* __restrict__ gout, const int32_t* __restrict__ idx, float* __restrict__ gin, int H,
+                    int W, int k, int nbx, int nby, uint32_t inv_w, uint32_t inv_lw)
+{
+    extern __shared__ uint32_t bits[];       // [words][kBX * ROWS], then the grad_out tile
+    constexpr int kQ = kBX * ROWS;
+    const int words = (k * RB + 31) / 32;
+    float* const g = reinterpret_cast<float*>(bits + words * kQ);
+    const int plane = blockIdx.x / (nbx * nby);
+    const int b = blockIdx.x - plane * nbx * nby;
+    const int by = b / nbx, bx = b - by * nbx;
+    const int r = (k - 1) / 2;
+    const long long base = (long long)plane * H * W;
+    const int X0 = bx * kBX, Y0 = by * ROWS;
+    const int lw = kBX + 2 * r, lh = ROWS + 2 * r;
+    for (int i = threadIdx.x; i < words * kQ; i += THREADS) bits[i] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < lw * lh; i += THREADS) {
+        const int y = (int)((uint32_t)i * inv_lw >> 20), x = i - y * lw;    // i / lw for i < 2^12
+        const int py = Y0 - r + y, px = X0 - r + x;
+        if (py < 0 || py >= H || px < 0 || px >= W) continue;
+        const long long o = base + (long long)py * W + px;
+        const uint32_t q = (uint32_t)idx[o];
+        g[i] = gout[o];
+        uint32_t qy = __umulhi(q, inv_w);                                   // q / W or one less
+        uint32_t qx = q - qy * (uint32_t)W;
+        if (qx >= (uint32_t)W) ++qy, qx -= (uint32_t)W;
+        const int ly = (int)qy - Y0, lx = (int)qx - X0;                     // place of q in the block
+        const int dy = y - ly, dx = x - lx;                                 // place of p in q's window
+        if (q < (uint32_t)(H * W) && (uint32_t)ly < (uint32_t)ROWS && (uint32_t)lx < (uint32_t)kBX &&
+            (uint32_t)dy < (uint32_t)k && (uint32_t)dx < (uint32_t)k)
+            atomicOr(&bits[(dy * RB >> 5) * kQ + ly * kBX + lx], 1u << ((dy * RB & 31) + dx));
     }
     __syncthreads();
     const int tx = threadIdx.x % kBX, ty = threadIdx.x / kBX;
-    const int y = Y0 + ty, x = X0 + tx;
-    if (y >= H || x >= W) return;
-    const uint32_t m = med[base + (long long)y * W + x];
-    // rows in order; within a row every read is independent of the match
-    // test, so the k reads of a row are in flight together
-    int found = -1;
-    for (int dy = 0; dy < k && found < 0; ++dy) {
-        const uint32_t* row = tile + (ty + dy) * lw + tx;
-        int first = k;
-#pragma unroll 8
-        for (int dx = 0; dx < k; ++dx)
-            first = (row[dx] == m && dx < first) ? dx : first;
-        if (first < k) {
-            const int gy = clampi(y - r + dy, 0, H - 1), gx = clampi(x - r + first, 0, W - 1);
-            found = gy * W + gx;
+    const int qx = X0 + tx;
+    if (qx >= W) return;
+    for (int ly = ty; ly < ROWS; ly += THREADS / kBX) {
+        if (Y0 + ly >= H) break;
+        float acc = 0.0f;
+        for (int w = 0; w < words; ++w) {
+            const float* p = g + (ly + w * (32 / RB)) * lw + tx;
+            uint32_t m = bits[w * kQ + ly * kBX + tx];
+            while (m) {
+                const int c = __builtin_ctz(m);
+                m &= m - 1;
+                acc = __fadd_rn(acc, p[c / RB * lw + c % RB]);
+            }
         }
+        gin[base + (long long)(Y0 + ly) * W + qx] = acc;
     }
-    idx[base + (long long)y * W + x] = found;
 }
 
+// Windows beyond 31: every q compares the argmedian of its k * k neighbours.
 __global__ void __launch_bounds__(kThreads)
 mf_grad_gather_kernel(const float* __restrict__ gout, const int32_t* __restrict__ idx,
                       float* __restrict__ gin, int H, int W, int k, int nbx, int nby)
@@ -101,22 +197,69 @@ mf_grad_gather_kernel(const float* __restrict__ gout, const int32_t* __restrict_
     gin[base + q] = acc;
 }
 
+namespace {
+
+template <class F>
+hipError_t allow_lds(F fn, size_t lds)
+{
+    return lds <= 64 * 1024 ? hipSuccess
+                            : hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+template <int K>
+hipError_t argmedian(const float* src, const float* med, int32_t* idx, unsigned blocks, size_t lds, int H, int W, int k,
+                     int nbx, int nby, hipStream_t stream)
+{
+    hipError_t e = allow_lds(mf_argmedian_kernel<K>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(mf_argmedian_kernel<K>, dim3(blocks), dim3(kThreads), lds, stream, (const uint32_t*)src,
+                       (const uint32_t*)med, idx, H, W, k, nbx, nby);
+    return hipGetLastError();
+}
+
+template <int RB, int ROWS, int THREADS>
+hipError_t grad_bits(const float* gout, const int32_t* idx, float* gin, int64_t planes, int H, int W, int k,
+                     hipStream_t stream)
+{
+    const int nbx = (W + kBX - 1) / kBX, nby = (H + ROWS - 1) / ROWS;
+    const long long blocks = planes * (long long)nbx * nby;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const int lw = kBX + k - 1, lh = ROWS + k - 1;
+    const size_t lds = (size_t)((k * RB + 31) / 32 * kBX * ROWS + lw * lh) * 4;
+    const uint32_t inv_w = W == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (unsigned)W);
+    const uint32_t inv_lw = ((1u << 20) + lw - 1) / lw;
+    hipError_t e = allow_lds(mf_grad_bits_kernel<RB, ROWS, THREADS>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((mf_grad_bits_kernel<RB, ROWS, THREADS>), dim3((unsigned)blocks), dim3(THREADS), lds, stream, gout,
+                       idx, gin, H, W, k, nbx, nby, inv_w, inv_lw);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t mf_ag_argmedian_launch(const float* src, const float* med, int32_t* idx, int64_t planes, int H,
                                   int W, int k, hipStream_t stream)
 {
-    const int nbx = (W + kBX - 1) / kBX, nby = (H + kBY - 1) / kBY;
+    const int nbx = (W + kBX - 1) / kBX, nby = (H + kAY - 1) / kAY;
     const long long blocks = planes * (long long)nbx * nby;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const size_t lds = (size_t)(kBX + k - 1) * (kBY + k - 1) * 4;
-    hipLaunchKernelGGL(mf_argmedian_kernel, dim3((unsigned)blocks), dim3(kThreads), lds, stream,
-                       (const uint32_t*)src, (const uint32_t*)med, idx, H, W, k, nbx, nby);
-    return hipGetLastError();
+    const size_t lds = (size_t)(kBX + k - 1) * (kAY + k - 1) * 4;
+    switch (k) {
+#define MF_CASE(K) case K: return argmedian<K>(src, med, idx, (unsigned)blocks, lds, H, W, k, nbx, nby, stream);
+    MF_CASE(3) MF_CASE(5) MF_CASE(7) MF_CASE(9) MF_CASE(11) MF_CASE(13) MF_CASE(15)
+#undef MF_CASE
+    default: return argmedian<0>(src, med, idx, (unsigned)blocks, lds, H, W, k, nbx, nby, stream);
+    }
 }
 
 hipError_t mf_ag_grad_launch(const float* gout, const int32_t* idx, float* gin, int64_t planes, int H, int W,
                              int k, hipStream_t stream)
 {
-    const int nbx = (W + kBX - 1) / kBX, nby = (H + kBY - 1) / kBY;
+    const int nbx = (W + kBX - 1) / kBX;
+    if (k <= 7) return grad_bits<8, 16, 256>(gout, idx, gin, planes, H, W, k, stream);
+    if (k <= 15) return grad_bits<16, 16, 512>(gout, idx, gin, planes, H, W, k, stream);
+    if (k <= 31) return grad_bits<32, 8, 512>(gout, idx, gin, planes, H, W, k, stream);
+    const int nby = (H + kBY - 1) / kBY;
     const long long blocks = planes * (long long)nbx * nby;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t lds = (size_t)(kBX + k - 1) * (kBY + k - 1) * 8;
