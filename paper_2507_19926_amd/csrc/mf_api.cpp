@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 
 #include "mf_hist.h"
@@ -135,22 +136,43 @@ bool hist_is_faster(int32_t dtype, int32_t k)
     return k >= from && mf_hist_supports(dtype, k, k);
 }
 
-// Calls of fewer pixels keep 16- and 32-bit data on the schedules: a ranked
-// region takes its 40-120 us (sort, first window, rows) however few there are,
-// the schedules' time falls with the pixels (us, ranked / schedule, one plane:
-// 16-bit 320^2 k = 23 44 / 33, 384^2 43 / 50, 512^2 43 / 58; float32 320^2
-// 66 / 52, 384^2 66 / 73, 512^2 66 / 94; k = 75 16-bit 256^2 78 / 67, 384^2
-// 78 / 177).
-bool too_small_to_rank(int32_t dtype, int64_t planes, int64_t H, int64_t W)
+// What a call of `pixels` pixels runs instead of the choice for large images
+// when it is small: a network's wave takes its 20-70 us (k = 9 to 21) and a
+// ranked region its 40-120 us however few there are, while a schedule's time
+// falls with the pixels and the 8-bit histograms start at 11 us. us, one plane
+// of uniform noise (normal float32), network / schedule / histograms:
+//   uint8   k = 9   512^2 18 / 628 / 13;  k = 11 1024^2 23 / 1642 / 19
+//   uint16  k = 17  384^2 37 / 28, 512^2 37 / 40;  k = 19  512^2 51 / 40, 768^2 52 / 74
+//           k = 21  256^2 68 / 24 / 42, 768^2 69 / 114 / 50, 1000x700 83 / 145 / 61
+//           k = 23  320^2 - / 33 / 44, 384^2 - / 50 / 43;  k = 75  256^2 - / 67 / 78
+//   float32 k = 17  256^2 32 / 22, 384^2 32 / 58;  k = 19  256^2 47 / 21, 384^2 47 / 57
+//           k = 23  320^2 - / 52 / 66, 384^2 - / 73 / 66
+enum class Small { no, schedule, histograms };
+Small small_choice(int32_t dtype, int32_t k, int64_t pixels)
 {
-    return dtype != MF_U8 && H * W < (1 << 17) && planes * H * W < (1 << 17);
+    if (dtype == MF_U8)
+        return (k == 9 && pixels <= (1 << 18)) || (k == 11 && pixels <= (1 << 20)) ? Small::histograms : Small::no;
+    if (pixels < (1 << 17) && hist_is_faster(dtype, k)) return Small::schedule;
+    if (dtype == MF_U16) {
+        if (k == 17) return pixels <= (1 << 17) ? Small::schedule : Small::no;
+        if (k == 19) return pixels <= (1 << 18) ? Small::schedule : Small::no;
+        if (k == 21) return pixels < (1 << 17) ? Small::schedule : pixels <= (1 << 20) ? Small::histograms : Small::no;
+        return Small::no;
+    }
+    return (k == 17 || k == 19) && pixels <= (1 << 16) ? Small::schedule : Small::no;
 }
 
-// Resolve (dtype, k, opt) to a variant and root tile; small: of a call that
-// is too_small_to_rank(). Host only.
+// planes * H * W, or a number beyond every line above
+int64_t pixels_of(int64_t planes, int64_t H, int64_t W)
+{
+    return planes > (1 << 21) || H > (1 << 21) || W > (1 << 21) ? (1 << 21) : planes * std::min<int64_t>(H * W, 1 << 21);
+}
+
+// Resolve (dtype, k, opt) to a variant and root tile; small: small_choice()
+// of the call. Host only.
 int32_t resolve(int32_t dtype, int32_t k, const mf_options* opt, int32_t* variant, int32_t* tw,
                 int32_t* th, const OblEntry** obl, int32_t* group = nullptr, int32_t* da_form = nullptr,
-                bool small = false)
+                Small small = Small::no)
 {
     mf_options o = {};
     if (opt) o = *opt;
@@ -166,22 +188,25 @@ int32_t resolve(int32_t dtype, int32_t k, const mf_options* opt, int32_t* varian
                     o.tile_h, k);
     if (o.form < 0 || o.form > 3) return fail(MF_ERR_CONFIG, "form %d not in {0, 1, 2, 3}", o.form);
     *obl = nullptr;
+    bool no_network = false;
     // measured choice for this (value class, k), when nothing was requested
     if (o.rows < 0) return fail(MF_ERR_CONFIG, "rows %d must be >= 0", o.rows);
     if (o.variant == MF_VARIANT_AUTO && !o.tile_w && !o.tile_h && !o.group && !o.form && !o.rows) {
-        if (hist_is_faster(dtype, k) && !small) {
+        if (small == Small::histograms || (hist_is_faster(dtype, k) && small == Small::no)) {
             *variant = MF_VARIANT_DATA_AWARE;
             *tw = *th = 1;
             if (group) *group = 1;
             if (da_form) *da_form = kDaFormHist;
             return MF_OK;
         }
+        no_network = small == Small::schedule;
         int cls = (dtype == MF_U8 || dtype == MF_U16) ? 0 : 1;
         if (dtype == MF_U16)
             for (const AutoEntry& a : kAutoTable)
                 if (a.cls == 2 && a.k == k) cls = 2;
         for (const AutoEntry& a : kAutoTable) {
             if (a.cls != cls || a.k != k) continue;
+            if (a.variant == MF_VARIANT_OBLIVIOUS && no_network) break;
             if (a.variant == MF_VARIANT_OBLIVIOUS) {
                 const OblEntry* e = find_obl(k, a.tw, a.th, a.group, a.form, a.rows);
                 if (e) {
@@ -202,7 +227,7 @@ int32_t resolve(int32_t dtype, int32_t k, const mf_options* opt, int32_t* varian
             break;  // a stale entry: fall back to the built-in order
         }
     }
-    if (o.variant != MF_VARIANT_DATA_AWARE) {
+    if (o.variant != MF_VARIANT_DATA_AWARE && !no_network) {
         const OblEntry* e =
             find_obl(k, o.tile_w, o.tile_h, o.group == 1 || o.group == 4 ? o.group : 0, o.form, o.rows);
         if (e) {
@@ -285,13 +310,10 @@ int32_t mf_internal_fail(int32_t code, const char* msg) { return fail(code, "%s"
 bool mf_internal_small_batch(const mf_image* imgs, int32_t n)
 {
     int64_t px = 0;
-    for (int i = 0; i < n; ++i)
-        if (imgs[i].dtype != MF_U8 && hist_is_faster(imgs[i].dtype, imgs[i].k)) {
-            if (!too_small_to_rank(imgs[i].dtype, 1, imgs[i].H, imgs[i].W)) return false;
-            px += imgs[i].H * imgs[i].W;
-            if (!too_small_to_rank(imgs[i].dtype, 1, 1, px)) return false;
-        }
-    return true;
+    for (int i = 0; i < n && px < (1 << 17); ++i)
+        if (imgs[i].dtype != MF_U8 && hist_is_faster(imgs[i].dtype, imgs[i].k))
+            px += pixels_of(1, imgs[i].H, imgs[i].W);
+    return px < (1 << 17);
 }
 
 int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t* tw, int32_t* th,
@@ -299,7 +321,8 @@ int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t*
                             bool small)
 {
     const OblEntry* e = nullptr;
-    int32_t rc = resolve(dtype, k, nullptr, variant, tw, th, &e, group, da_form, small && dtype != MF_U8);
+    int32_t rc = resolve(dtype, k, nullptr, variant, tw, th, &e, group, da_form,
+                         small && dtype != MF_U8 && hist_is_faster(dtype, k) ? Small::schedule : Small::no);
     if (rc) return rc;
     // the column-strip form has no batched kernel: plans use k's default
     // network
@@ -412,7 +435,8 @@ int32_t median_filter_rect(const void* src, void* dst, int64_t planes, int64_t p
         return fail(MF_ERR_CONFIG, "no data-aware schedule for the %dx%d window", kw, kh);
     // without a network: sliding histograms instead of the schedule (30 MP RGB
     // 8-bit frame: 21x13 0.45 ms against 9.9, 31x29 0.87 against 22 on noise)
-    if (variant == MF_VARIANT_AUTO && mf_hist_supports(dtype, kw, kh) && !too_small_to_rank(dtype, planes, H, W))
+    if (variant == MF_VARIANT_AUTO && mf_hist_supports(dtype, kw, kh) &&
+        (dtype == MF_U8 || pixels_of(planes, H, W) >= (1 << 17)))   // the line of small_choice()
         return hip_status(mf_hist_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, dtype,
                                          kw, kh, (hipStream_t)stream),
                           "sliding-histogram kernel launch");
@@ -474,7 +498,8 @@ int32_t median_filter_planes(const void* src, void* dst, int64_t planes, int64_t
                                          st);
     int32_t variant = 0, tw = 0, th = 0, group = 0, da_form = 0;
     const OblEntry* e = nullptr;
-    rc = resolve(dtype, k, opt, &variant, &tw, &th, &e, &group, &da_form, too_small_to_rank(dtype, planes, H, W));
+    rc = resolve(dtype, k, opt, &variant, &tw, &th, &e, &group, &da_form,
+                 small_choice(dtype, k, pixels_of(planes, H, W)));
     if (rc) return rc;
     if (variant == MF_VARIANT_OBLIVIOUS) {
         mf_launch_fn fn = (dtype == MF_U8 || dtype == MF_U16) ? e->p16 : e->u32;

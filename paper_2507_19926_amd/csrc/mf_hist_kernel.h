@@ -155,6 +155,38 @@ struct Hist {
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 
+    // The wave's number among search (0 .. kWaves - 1) and slide waves. With
+    // four waves to a work-group (P = 2) and two work-groups to a CU, each
+    // SIMD has two waves; up to about 40 counter updates a row a search wave
+    // has more to do than a slide wave, so the work-group that holds the
+    // lower half of the CU's LDS searches on SIMDs 0 and 1, the other one on 2
+    // and 3, and no two searches share a SIMD. Clocks a row step, smooth image
+    // (uniform noise): k = 7 825 (3410) with roles by wave number, 790 (2690)
+    // now; k = 17 1005 (1620), 940 (1390); k = 35 1430 (1560), 1270 (1390);
+    // k = 65 2010, 1970; k = 75 2270, 2370, so the widest windows keep the wave
+    // numbers, and the boxes beyond 9 (k = 15 1.71 ms, 1.75).
+    // Only the speed rests on what the registers say: unless the four waves
+    // are on four SIMDs, roles go by wave number.
+    static constexpr bool kBySimd = P == 2 && (Z == 1 ? KW <= 67 : Z <= 9);
+    static __device__ __forceinline__ int role()
+    {
+        int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        if constexpr (kBySimd) {
+            constexpr int kSimd = 4 | 4 << 6 | 1 << 11;          // HW_ID bits 4..5
+            constexpr int kLdsBase = 6 | 0 << 6 | 11 << 11;      // LDS_ALLOC bits 0..11
+            const uint32_t simd = __builtin_amdgcn_s_getreg(kSimd);
+            const uint32_t upper = __builtin_amdgcn_s_getreg(kLdsBase) != 0 ? 2u : 0u;
+            if (__lane_id() == 0) *(lds_u32*)(uintptr_t)(kStage + 4 * wave) = 1u << simd;
+            __syncthreads();
+            uint32_t all = 0;
+            for (int i = 0; i < 4; ++i) all |= *(const lds_u32*)(uintptr_t)(kStage + 4 * i);
+            if (__builtin_amdgcn_readfirstlane((int)all) == 15) wave = (int)(simd ^ upper);
+            wave = __builtin_amdgcn_readfirstlane(wave);
+            __syncthreads();
+        }
+        return wave;
+    }
+
     // Rows [y0, y1) of the kCols columns from x0 on. For boxes (Z > 1) of
     // slice z: src is the volume, slices `slice` bytes apart, D of them.
     static __device__ __forceinline__ void strip(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
@@ -162,7 +194,7 @@ struct Hist {
                                                  int D = 1, long long slice = 0, int z = 0)
     {
         const int lane = (int)__lane_id();
-        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int wave = role();
         for (uint32_t i = threadIdx.x * 16; i < kStage; i += kThreads * 16)
             *(lds_u32x4*)(uintptr_t)i = u32x4{0, 0, 0, 0};
         // row y of the q-th slice of the box

@@ -10,19 +10,27 @@
 // With v_min3 / v_max3 / v_med3 that is three instructions per sorted column
 // and four per output.
 //
-// Each wave owns a strip of 64 lanes x P pixels (one 8-byte chunk per lane and
-// row for 8-bit data, 16 bytes otherwise) and R = 32 output rows. A lane streams the R + 2 input rows of its
-// chunk through registers with the next 8 rows always in flight (no LDS, no
-// barriers), keeps three rows and a sliding window of three sorted columns,
-// and stores each output row as one chunk. The columns just left and
-// right of a lane's chunk come from the neighbouring lanes by a lane shuffle;
-// lanes 0 and 63 load theirs. A work-group stacks 4 waves vertically.
+// Each wave owns a strip of 64 lanes x P pixels (one 16-byte chunk per lane and
+// row, 8 bytes for small 8-bit images) and R = 4 output rows. A lane loads the
+// R + 2 input rows of its chunk into registers at once (no LDS, no barriers),
+// keeps three rows and a sliding window of three sorted columns, and stores
+// each output row as one chunk. The columns just left and right of a lane's
+// chunk come from the neighbouring lanes by a lane shuffle; lanes 0 and 63
+// load theirs. A work-group stacks 4 waves vertically.
+//
+// Bound: HBM for large images (30 MP RGB uint8 41 us, 4.4 TB/s), the launch
+// for small ones. Few rows to a wave cost (R + 2) / R of the loads (mostly from
+// L2) but give the chip 8 times the waves of R = 32: us for R = 2, 4, 8, 16, 32,
+// 16-byte chunks, 30 MP RGB uint8 45, 41, 42, 45, 57 (8-byte chunks 55, 47, 47,
+// 51, 55); 512 x 512 uint8, 8-byte chunks 3.7, 4.0, 5.8, 8.9, 15.3 (16-byte 4.0,
+// 5.3, 8.0, 13.5, 24.7); 4096^2 uint16 14.6, 13.5, 14.7, 15.0, 17.4; 4096^2
+// float32 26.6, 25.6, 26.9, 25.0, 25.6.
 #include "mf_internal.h"
 
 namespace {
 
-constexpr int kStripRows = 32;     // output rows per wave
-constexpr int kStripDepth = 8;     // input rows loaded ahead of their use
+constexpr int kStripRows = 4;      // output rows per wave
+constexpr int kStripDepth = 6;     // input rows loaded ahead of their use: all
 constexpr int kStripWaves = 4;     // waves per work-group, stacked vertically
 
 __device__ __forceinline__ uint32_t smin(uint32_t a, uint32_t b) { return a < b ? a : b; }
@@ -265,8 +273,12 @@ hipError_t strip3_launch(const void* src, void* dst, int planes, long long plane
 hipError_t mf_strip3_launch_p16(const void* src, void* dst, int planes, long long plane_stride, int H, int W,
                                 long long pitch, int dtype, hipStream_t st)
 {
-    return dtype == MF_U8 ? strip3_launch<1, 8>(src, dst, planes, plane_stride, H, W, pitch, dtype, st)
-                          : strip3_launch<2, 16>(src, dst, planes, plane_stride, H, W, pitch, dtype, st);
+    if (dtype == MF_U16) return strip3_launch<2, 16>(src, dst, planes, plane_stride, H, W, pitch, dtype, st);
+    // 8-byte chunks while the image leaves waves to want (1024^2 4.1 us against
+    // 4.8, 2048^2 5.1 against 5.2, 4096^2 11.4 against 10.7)
+    return (long long)planes * H * W < (1LL << 22)
+               ? strip3_launch<1, 8>(src, dst, planes, plane_stride, H, W, pitch, dtype, st)
+               : strip3_launch<1, 16>(src, dst, planes, plane_stride, H, W, pitch, dtype, st);
 }
 
 hipError_t mf_strip3_launch_u32(const void* src, void* dst, int planes, long long plane_stride, int H, int W,
