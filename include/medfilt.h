@@ -83,10 +83,13 @@ typedef struct mf_options {
                          shared by three windows, rows streamed through
                          registers); data-aware: 1 = rounds per recursion
                          level, 2 = rounds over the whole schedule, 3 =
-                         sliding histograms (MF_U8, k >= 13: root tile 1x1,
-                         the library's choice there; not among the
-                         configurations mf_list_configs enumerates, there
-                         is nothing in it to tune); 0 = library's          */
+                         sliding histograms (root tile 1x1; where they are
+                         the library's choice: MF_U8 k >= 13, MF_U16 k >= 23,
+                         32-bit k >= 21; not among the configurations that
+                         mf_list_configs enumerates, as there is nothing in
+                         them to tune; by default 16- and 32-bit calls of
+                         fewer than 131072 pixels run the schedule
+                         instead); 0 = library's                            */
     int32_t rows;     /* oblivious: tile rows per wave; 0 = library's       */
 } mf_options;
 
@@ -147,8 +150,8 @@ int32_t mf_max_rect_side(void);
  * kw == kh answers as mf_query_config with default options; otherwise
  * MF_VARIANT_OBLIVIOUS and the network's root tile when one is compiled for
  * the shape, else MF_VARIANT_DATA_AWARE and the generated schedule's tile
- * (the MF_VARIANT_AUTO choice; MF_U8 runs such shapes by sliding histograms,
- * MF_VARIANT_DATA_AWARE runs the schedule for every dtype). Errors as
+ * (MF_VARIANT_AUTO runs such shapes by sliding histograms for all but small
+ * images, MF_VARIANT_DATA_AWARE by the schedule). Errors as
  * median_filter_rect's window and dtype checks (MF_ERR_NULL for a NULL
  * output pointer). */
 int32_t mf_query_rect_config(int32_t dtype, int32_t kw, int32_t kh, int32_t* variant,
@@ -164,7 +167,9 @@ int32_t mf_query_rect_config(int32_t dtype, int32_t kw, int32_t kh, int32_t* var
 int32_t mf_peak_minmax(void* out, int32_t blocks, int32_t iters, void* stream);
 
 /* The configuration median_filter_ex would run for (dtype, k, opt): the
- * variant and root tile actually used. Host-only; no GPU needed. */
+ * variant and root tile actually used. Without a request (MF_VARIANT_AUTO)
+ * that is the choice for large images; small ones may run another variant,
+ * with the same results. Host-only; no GPU needed. */
 int32_t mf_query_config(int32_t dtype, int32_t k, const mf_options* opt,
                         int32_t* variant, int32_t* tile_w, int32_t* tile_h);
 

@@ -20,7 +20,20 @@ def dtype_code(t: torch.dtype) -> int:
 
 
 def _stream_handle(dev: torch.device):
-    return torch.cuda.current_stream(dev).cuda_stream
+    # the raw handle of torch.cuda.current_stream(dev), without the Stream
+    # object around it
+    return torch._C._cuda_getCurrentRawStream(dev.index)
+
+
+def _packed(x: torch.Tensor) -> bool:
+    """Whether x has the strides of a new tensor of its shape, every one of
+    them (is_contiguous() overlooks those of dimensions of size 1)."""
+    n = 1
+    for size, stride in zip(reversed(x.shape), reversed(x.stride())):
+        if stride != n:
+            return False
+        n *= size
+    return n > 0
 
 
 def median_filter(x: torch.Tensor, k: int, out: torch.Tensor | None = None,
@@ -38,6 +51,17 @@ def median_filter(x: torch.Tensor, k: int, out: torch.Tensor | None = None,
     if x.dim() < 2:
         raise ValueError("median_filter needs (..., H, W)")
     code = dtype_code(x.dtype)
+    if out is None and variant == 0 and tile is None and not (group or form or rows) and _packed(x):
+        # the usual call: packed planes, nothing asked for. What follows below
+        # comes to the same call, by views and an options record that take
+        # longer than a small image's kernel (512 x 512 uint8, k = 3: the
+        # kernel 4 us, a call 11.2 us by the long way)
+        out = torch.empty(x.shape, dtype=x.dtype, device=x.device)
+        H, W, es = x.shape[-2], x.shape[-1], x.element_size()
+        n = x.numel() // (H * W)
+        _lib.check(_lib.lib().median_filter_planes(x.data_ptr(), out.data_ptr(), n, H * W * es, H, W, W * es, code,
+                                                   int(k), _lib.MF_BORDER_REPLICATE, None, _stream_handle(x.device)))
+        return out
     if x.stride(-1) != 1:
         x = x.contiguous()
     H, W = x.shape[-2], x.shape[-1]
