@@ -17,6 +17,11 @@ struct HistKernelInfo {
     const void* batched;    // null where no square window uses it
     int threads, cols, rows;   // output columns of a work-group; rows of a batched block
     size_t lds;
+    // ranked kernels: most output rows of a region; those beyond `rows` run the
+    // tall kernel
+    int max_rows = 0;
+    const void* tall = nullptr;
+    size_t tall_lds = 0;
 };
 
 // Whether the kw x kh window (kw columns, kh rows, both odd) has a kernel.

@@ -18,7 +18,8 @@ bool mf_hist_kernel_box(int k, HistKernelInfo* h);
 namespace {
 
 constexpr int kMaxDevices = 64;
-constexpr int kSlots = 8 * 38 + 16;   // slot_of() of windows, then boxes
+constexpr int kTallSlots = 8 * 38 + 16;   // slot_of() of windows, boxes, then tall ranked kernels
+constexpr int kSlots = kTallSlots + 38;
 
 // All counts of the window fit the one-word layout: 4 bits for a column's
 // kh values, 8 for the kw - 3 shared columns'.
@@ -86,11 +87,11 @@ int strip_rows(int H, long long per_strip, long long first, int cus)
 // noise, k = 25..75): 5 (16-bit) or 10 (32-bit) for a value of the footprint,
 // loaded, sorted and listed, 300 for a row of the first window, 1600 for an
 // output row slid, searched and walked; one region to a CU.
-int rank_rows(int H, long long per_strip, int fw, int kh, bool wide, int cus)
+int rank_rows(int H, int max_rows, long long per_strip, int fw, int kh, bool wide, int cus)
 {
     long long best = -1;
-    int R = 64;
-    for (int r = 64; r >= 8; r -= 8) {
+    int R = max_rows;
+    for (int r = max_rows; r >= 8; r -= 8) {
         const long long regions = (H + r - 1) / r * per_strip;
         const int used = r < H ? r : H;
         const long long cost = (regions + cus - 1) / cus *
@@ -123,13 +124,16 @@ hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plan
     int dev = 0, cus = 0;
     hipError_t e = device(&dev, &cus);
     if (e != hipSuccess) return e;
-    e = allow_lds(k.planes, slot_of(dtype, kw, kh, false), dev);
-    if (e != hipSuccess) return e;
     const int ncol = (W + k.cols - 1) / k.cols;
     const bool rank = dtype != MF_U8;
-    const int R = rank ? rank_rows(H, (long long)ncol * planes, k.cols + kw - 1, kh, dtype != MF_U16, cus)
+    const int R = rank ? rank_rows(H, k.max_rows, (long long)ncol * planes, k.cols + kw - 1, kh, dtype != MF_U16, cus)
                        : strip_rows(H, (long long)ncol * planes, kh / 4 + 8, cus);
     int is_float = dtype == MF_F32;
+    const bool tall = rank && R > k.rows;
+    const void* fn = tall ? k.tall : k.planes;
+    const size_t lds = tall ? k.tall_lds : k.lds;
+    e = allow_lds(fn, tall ? kTallSlots + kw / 2 : slot_of(dtype, kw, kh, false), dev);
+    if (e != hipSuccess) return e;
     const int ns = (H + R - 1) / R;
     if ((long long)ncol * ns > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     for (int p0 = 0; p0 < planes; p0 += 65535) {     // grid rows are planes
@@ -137,7 +141,7 @@ hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plan
         const unsigned char* s8 = (const unsigned char*)src + p0 * plane_stride;
         unsigned char* d8 = (unsigned char*)dst + p0 * plane_stride;
         void* args[] = {&s8, &d8, &H, &W, &pitch, &plane_stride, (void*)&ncol, (void*)&R, &kh, &is_float};   // is_float: ranked kernels
-        e = hipLaunchKernel(k.planes, dim3((unsigned)(ncol * ns), np), dim3(k.threads), args, k.lds, stream);
+        e = hipLaunchKernel(fn, dim3((unsigned)(ncol * ns), np), dim3(k.threads), args, lds, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

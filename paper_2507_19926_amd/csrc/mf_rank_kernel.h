@@ -26,7 +26,8 @@ namespace {
 typedef __attribute__((address_space(3))) uint16_t lds_u16;
 
 constexpr int kRankThreads = 512;
-constexpr int kRankRows = 64;            // most output rows of a region
+constexpr int kRankRows = 64;            // output rows of a batched block
+constexpr int kRankValues = 27900;       // most values of a footprint: 75 columns' of 64 rows
 
 __device__ __forceinline__ uint32_t rank_key(uint32_t b, bool is_float)
 {
@@ -35,12 +36,21 @@ __device__ __forceinline__ uint32_t rank_key(uint32_t b, bool is_float)
 
 // V: uint16_t or uint32_t (float32 by its ordered key). KHM: most rows of the
 // window.
-template <int KW, int KHM, class V>
+template <int KW, int KHM, class V, bool TALL = false>
 struct Rank {
     typedef Hist<KW, 2> Hs;
     static constexpr int kCols = Hs::kCols;
     static constexpr int FW = kCols + KW - 1;                 // footprint columns
-    static constexpr int FHM = kRankRows + KHM - 1;           // most footprint rows
+    // Most output rows: 64, or (TALL) as many as the LDS sorts the footprint
+    // of, up to 128: the rows shared with the regions above and below are
+    // sorted again in those. The longer runs of a thread cost the shorter
+    // regions time, and 16-bit data more than the rows save (4096^2, 64 and
+    // tall: float32 k = 25 0.93, 0.89 ms, k = 35 1.01, 0.94; uint16 k = 25
+    // 0.70, 0.73, k = 35 0.74, 0.74).
+    static constexpr int kFit = (kRankValues / FW - (KHM - 1)) / 8 * 8;
+    static constexpr int kRows = !TALL ? kRankRows : kFit < 128 ? kFit : 128;
+    static_assert(kRows >= kRankRows, "a batched block is a region");
+    static constexpr int FHM = kRows + KHM - 1;               // most footprint rows
     static constexpr int FS = Hs::kRow;                       // bytes of a row of bucket numbers
     static constexpr int E = ((FW * FHM + kRankThreads - 1) / kRankThreads) | 1;   // most values of a thread
     static constexpr int SM = ((FW * FHM + 255) / 256 + 7) / 8 * 8;   // most values of a bucket
@@ -56,6 +66,18 @@ struct Rank {
 
     static __device__ __forceinline__ uint32_t ld(uint32_t a) { return *(const lds_u32*)(uintptr_t)a; }
     static __device__ __forceinline__ void st(uint32_t a, uint32_t v) { *(lds_u32*)(uintptr_t)a = v; }
+
+    // Inclusive sum over the lanes of a wave.
+    static __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+    {
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);    // row_shr 1
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);    // row_shr 2
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);    // row_shr 4
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);    // row_shr 8
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast 15
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast 31
+        return v;
+    }
 
     // One stable pass over the four bits from `shift` on of key; pos follows.
     static __device__ __forceinline__ void pass(uint32_t (&key)[E], uint32_t (&pos)[kPacked ? 1 : E], int shift, int t, int eu, int n)
@@ -82,12 +104,7 @@ struct Rank {
             uint32_t s = 0;
 #pragma unroll
             for (int i = 0; i < 8; ++i) s += v[q][i];
-            uint32_t inc = s;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t up = (uint32_t)__shfl_up((int)inc, o);
-                inc += lane >= o ? up : 0u;
-            }
+            const uint32_t inc = wave_sum(s);
             run[q] = inc - s;
             if (lane == 63) st(kTot + (uint32_t)(wave * 2 + q) * 4, inc);
         }
@@ -372,12 +389,12 @@ struct Rank {
     }
 };
 
-template <int KW, int KHM, class V>
+template <int KW, int KHM, class V, bool TALL>
 __global__ void __launch_bounds__(kRankThreads)
 mf_rank_kernel(const unsigned char* __restrict__ src, unsigned char* dst, int H, int W, long long pitch,
                long long plane_stride, int ncol, int R, int kh, int is_float)
 {
-    typedef Rank<KW, KHM, V> Rk;
+    typedef Rank<KW, KHM, V, TALL> Rk;
     const int cb = (int)blockIdx.x % ncol, s = (int)blockIdx.x / ncol;
     const long long po = (long long)blockIdx.y * plane_stride;   // plane = blockIdx.y
     Rk::region(src + po, dst + po, H, W, pitch, cb * Rk::kCols, s * R, min((s + 1) * R, H), kh, is_float != 0);
@@ -411,7 +428,15 @@ HistKernelInfo rank_kernel()
     typedef Rank<KW, KHM, V> Rk;
     const void* b = nullptr;
     if constexpr (BATCHED) b = (const void*)mf_rank_kernel_batched<KW, KHM, V>;
-    return {(const void*)mf_rank_kernel<KW, KHM, V>, b, kRankThreads, Rk::kCols, kRankRows, Rk::kLds};
+    HistKernelInfo k = {(const void*)mf_rank_kernel<KW, KHM, V, false>, b, kRankThreads, Rk::kCols, kRankRows, Rk::kLds,
+                        Rk::kRows};
+    if constexpr (sizeof(V) == 4 && Rk::kFit > kRankRows) {
+        typedef Rank<KW, KHM, V, true> Tall;
+        k.tall = (const void*)mf_rank_kernel<KW, KHM, V, true>;
+        k.tall_lds = Tall::kLds;
+        k.max_rows = Tall::kRows;
+    }
+    return k;
 }
 
 }  // namespace

@@ -69,6 +69,19 @@ def test_pitched_planes(dtype):
         assert got[p].tobytes() == want.tobytes()
 
 
+@pytest.mark.parametrize("k", [21, 31, 33, 51, 75])
+@pytest.mark.parametrize("dtype", [np.uint32, np.float32])
+def test_tall_regions(k, dtype):
+    """32-bit images large enough that the launch takes regions of more than
+    64 rows (where the window leaves room for them), the last one ragged."""
+    img = next(_images(dtype, 1211, 2100, seed=k))
+    got = median_filter(torch.from_numpy(img).cuda(), k).cpu().numpy()
+    g = np.random.default_rng(k)
+    ys = np.concatenate([g.integers(0, 1211, 1500), np.arange(1211), np.full(64, 1210)])
+    xs = np.concatenate([g.integers(0, 2100, 1500), np.full(1211, 2099), g.integers(0, 2100, 64)])
+    assert got[ys, xs].tobytes() == oracle.median_points(img, k, ys, xs).tobytes()
+
+
 def test_many_regions_sampled():
     """Several rounds of regions over the chip, in strips of the rows the
     launch chooses, against sampled pixels of the oracle."""
