@@ -84,9 +84,9 @@ int strip_rows(int H, long long per_strip, long long first, int cus)
 }
 
 // Output rows of a ranked region, by the measured clocks of its parts (uniform
-// noise, k = 25..75): 5 (16-bit) or 10 (32-bit) for a value of the footprint,
-// loaded, sorted and listed, 300 for a row of the first window, 1600 for an
-// output row slid, searched and walked; one region to a CU.
+// noise, k = 25..75): 4 (16-bit), 9 (32-bit) or 12 (32-bit, tall kernel) for a
+// value of the footprint, loaded, sorted and listed, 300 for a row of the first
+// window, 1600 for an output row slid, searched and walked; one region to a CU.
 int rank_rows(int H, int max_rows, long long per_strip, int fw, int kh, bool wide, int cus)
 {
     long long best = -1;
@@ -94,8 +94,9 @@ int rank_rows(int H, int max_rows, long long per_strip, int fw, int kh, bool wid
     for (int r = max_rows; r >= 8; r -= 8) {
         const long long regions = (H + r - 1) / r * per_strip;
         const int used = r < H ? r : H;
+        const long long value = !wide ? 4 : r <= 64 ? 9 : 12;
         const long long cost = (regions + cus - 1) / cus *
-                               ((wide ? 10LL : 5LL) * fw * (used + kh - 1) + 300LL * kh + 1600LL * used + 5000);
+                               (value * fw * (used + kh - 1) + 300LL * kh + 1600LL * used + 5000);
         if (best < 0 || cost < best) best = cost, R = r;
     }
     return R;

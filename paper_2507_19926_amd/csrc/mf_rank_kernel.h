@@ -42,17 +42,16 @@ struct Rank {
     static constexpr int kCols = Hs::kCols;
     static constexpr int FW = kCols + KW - 1;                 // footprint columns
     // Most output rows: 64, or (TALL) as many as the LDS sorts the footprint
-    // of, up to 128: the rows shared with the regions above and below are
-    // sorted again in those. The longer runs of a thread cost the shorter
-    // regions time, and 16-bit data more than the rows save (4096^2, 64 and
-    // tall: float32 k = 25 0.93, 0.89 ms, k = 35 1.01, 0.94; uint16 k = 25
-    // 0.70, 0.73, k = 35 0.74, 0.74).
+    // of, up to 128: a plane of few regions then takes a round of the CUs less
+    // (float32 k = 25, 1531 x 2049: 104 rows 187 us, 64 rows 218), the runs of a
+    // thread are longer and slower (4096^2: 0.89 ms against 0.84).
     static constexpr int kFit = (kRankValues / FW - (KHM - 1)) / 8 * 8;
     static constexpr int kRows = !TALL ? kRankRows : kFit < 128 ? kFit : 128;
     static_assert(kRows >= kRankRows, "a batched block is a region");
     static constexpr int FHM = kRows + KHM - 1;               // most footprint rows
     static constexpr int FS = Hs::kRow;                       // bytes of a row of bucket numbers
     static constexpr int E = ((FW * FHM + kRankThreads - 1) / kRankThreads) | 1;   // most values of a thread
+    static constexpr bool kFull = sizeof(V) == 2 || E <= 45;  // runs that fit the registers (see pass)
     static constexpr int SM = ((FW * FHM + 255) / 256 + 7) / 8 * 8;   // most values of a bucket
     static constexpr uint32_t kIds = kStage;
     static constexpr uint32_t kList = kIds + (FS * FHM + 15) / 16 * 16;
@@ -80,7 +79,14 @@ struct Rank {
     }
 
     // One stable pass over the four bits from `shift` on of key; pos follows.
-    static __device__ __forceinline__ void pass(uint32_t (&key)[E], uint32_t (&pos)[kPacked ? 1 : E], int shift, int t, int eu, int n)
+    // FULL: eu == E, and the loops over a thread's values have no conditions, so
+    // the compiler keeps their LDS accesses in flight together: 4096^2 uint16
+    // k = 35 0.67 ms against 0.73, k = 75 1.00 against 1.12, float32 k = 25 0.84
+    // against 0.93. Long runs of 32-bit data then spill (k = 75 1.56 against
+    // 1.50 ms) and keep the conditions.
+    template <bool FULL>
+    static __device__ __forceinline__ void pass(uint32_t (&key)[E], uint32_t (&pos)[kPacked ? 1 : E], int shift, int t,
+                                                int eu, int n)
     {
         const uint32_t cnt = kCnt + (uint32_t)t * 4;
 #pragma unroll
@@ -88,7 +94,7 @@ struct Rank {
         uint32_t r[E];
 #pragma unroll
         for (int j = 0; j < E; ++j)
-            if (j < eu) r[j] = __hip_atomic_fetch_add((lds_u32*)(uintptr_t)(cnt + ((key[j] >> shift) & 15u) * (kRankThreads * 4)), 1u,
+            if (FULL || j < eu) r[j] = __hip_atomic_fetch_add((lds_u32*)(uintptr_t)(cnt + ((key[j] >> shift) & 15u) * (kRankThreads * 4)), 1u,
                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __syncthreads();
         // exclusive sums, digit by digit and thread by thread: a wave takes
@@ -129,20 +135,20 @@ struct Rank {
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < E; ++j) if (j < eu) {
+        for (int j = 0; j < E; ++j) if (FULL || j < eu) {
             r[j] = (r[j] + ld(cnt + ((key[j] >> shift) & 15u) * (kRankThreads * 4))) * 4;
             st(r[j], key[j]);
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < E; ++j) if (j < eu) key[j] = ld((uint32_t)(t * eu + j) * 4);
+        for (int j = 0; j < E; ++j) if (FULL || j < eu) key[j] = ld((uint32_t)(t * eu + j) * 4);
         __syncthreads();
         if constexpr (!kPacked) {
 #pragma unroll
-            for (int j = 0; j < E; ++j) if (j < eu) st(r[j], pos[j]);
+            for (int j = 0; j < E; ++j) if (FULL || j < eu) st(r[j], pos[j]);
             __syncthreads();
 #pragma unroll
-            for (int j = 0; j < E; ++j) if (j < eu) pos[j] = ld((uint32_t)(t * eu + j) * 4);
+            for (int j = 0; j < E; ++j) if (FULL || j < eu) pos[j] = ld((uint32_t)(t * eu + j) * 4);
             __syncthreads();
         }
     }
@@ -192,19 +198,25 @@ struct Rank {
             // row-major runs, one to a thread, of an odd number of values (a
             // run then starts in another LDS bank than its neighbours'); the
             // fillers come last and stay last (stable sort)
-            const int eu = ((n + kRankThreads - 1) / kRankThreads) | 1;
+            const int need = ((n + kRankThreads - 1) / kRankThreads) | 1;
+            const bool full = kFull && need * 8 >= E * 7;
+            const int eu = full ? E : need;
             uint32_t key[E], pos[kPacked ? 1 : E];
 #pragma unroll
             for (int j = 0; j < E; ++j) {
                 const int i = t * eu + j, fy = i / FW, fx = i - fy * FW;
                 const bool real = j < eu && i < n;
                 const uint32_t p = real ? (uint32_t)(fy << 8 | fx) : 0xffffu;
-                const uint32_t k = real ? ld((uint32_t)i * 4) : 0xffffffffu;
+                const uint32_t v = ld((uint32_t)i * 4);       // in the buffer, whatever i
+                const uint32_t k = real ? v : 0xffffffffu;
                 if constexpr (kPacked) key[j] = k << 16 | p;
                 else key[j] = k, pos[j] = p;
             }
             __syncthreads();
-            for (int s = kPacked ? 16 : 0; s < 32; s += 4) pass(key, pos, s, t, eu, n);
+            for (int s = kPacked ? 16 : 0; s < 32; s += 4) {
+                if (full) pass<kFull>(key, pos, s, t, eu, n);
+                else pass<false>(key, pos, s, t, eu, n);
+            }
             // bucket numbers and list; i / S = i * inv >> 22 for i < 2^22 / S
             static_assert((long long)E * kRankThreads * SM < (1 << 22) && SM <= 255, "i / S by one product");
             const uint32_t inv = (uint32_t)(((1 << 22) + S - 1) / S);
