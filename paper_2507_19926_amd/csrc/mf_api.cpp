@@ -123,13 +123,13 @@ const OblEntry* find_obl(int k, int tw, int th, int nw, int form, int rows)
 // walks from one row's median to the next, far on noise with a small window).
 // Per 30 MP RGB frame, smooth image / uniform noise against the network or
 // the schedule: k = 11 0.36 / 0.79 ms against 0.55 ms; k = 15 0.42 / 0.70
-// against 1.14; k = 17 0.60 / 1.04 against 1.42; k = 25 0.72 / 0.99 against
-// 10.4; k = 75 1.41 / 1.43 against 39.8.
+// against 1.14; k = 17 0.54 / 0.96 against 1.41; k = 25 0.70 / 0.97 against
+// 10.4; k = 75 1.42 / 1.43 against 40.
 // 16- and 32-bit data rank the values first, so their line lies where the
 // networks end or slow down (4096^2, uniform 16-bit and normal float32 data):
-// 16-bit k = 21 0.70 ms against the network's 0.68, k = 25 0.68 against 3.16
-// (schedule), k = 75 1.12 against 12.8; float32 k = 19 0.93 against 0.96, k = 21 0.96 against 1.84, k = 25 0.93
-// against 5.47, k = 75 1.53 against 24.3.
+// 16-bit k = 21 0.70 ms against the network's 0.67, k = 25 0.63 against 3.2
+// (schedule), k = 75 1.01 against 12.8; float32 k = 19 0.93 against 0.94,
+// k = 21 0.96 against 1.80, k = 25 0.84 against 6.3, k = 75 1.50 against 24.3.
 bool hist_is_faster(int32_t dtype, int32_t k)
 {
     const int32_t from = dtype == MF_U8 ? 13 : dtype == MF_U16 ? 23 : 21;

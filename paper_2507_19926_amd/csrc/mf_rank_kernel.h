@@ -17,6 +17,12 @@
 //
 // The LDS holds one region per CU: 66 KB of counters, the bucket numbers, and
 // the list (2 bytes a value); the sort's buffer lies over all of them.
+//
+// Bound: one region's latency, two waves to a SIMD. Of a 16-bit region at
+// k = 35 the load takes about 12 thousand clocks, the four sort passes 45, the
+// bucket numbers 9, the first window 11, the 64 row steps 70 and the walk 32;
+// 32-bit data have eight passes over twice the bytes. 4096^2, before (schedule) and now:
+// uint16 k = 35 4.33 / 0.66 ms; float32 k = 25 6.3 / 0.84 ms.
 #pragma once
 
 #include "mf_hist_kernel.h"
