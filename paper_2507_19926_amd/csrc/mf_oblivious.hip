@@ -31,6 +31,8 @@
 // no bank conflicts in the network stage.
 #pragma once
 
+#include <type_traits>
+
 #include "mf_internal.h"
 
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
@@ -95,12 +97,12 @@ struct MfObGeom {
     static constexpr int STG_CHUNKS = (ROWS * NCH + 63) / 64 * 64;
 };
 
-// Global loads of one block's footprint union (plain and batched forms),
-// issued all at once into registers, then scattered into LDS.
+// Global loads of one block's footprint union (plain and batched forms,
+// packed types), issued all at once into registers, then scattered into LDS.
 template <class V, int K, int KH, int TW, int TH, int RY, int NW>
 struct MfObPrefetch {
     using G = MfObGeom<V, K, KH, TW, TH, RY, NW>;
-    uint32_t va[G::U], vb[G::PACK ? G::U : 1];
+    uint32_t va[G::U], vb[G::U];
     bool fast;
 };
 
@@ -113,9 +115,9 @@ mf_obl_issue(const unsigned char* __restrict__ src, int H, int W, long long pitc
              MfObPrefetch<V, K, KH, TW, TH, RY, NW>& pf)
 {
     using G = MfObGeom<V, K, KH, TW, TH, RY, NW>;
-    const int es = G::PACK ? (dtype == MF_U8 ? 1 : 2) : 4;
+    const int es = dtype == MF_U8 ? 1 : 2;
     const int gx0 = X0 - G::RX;
-    const int span = G::PACK ? (G::BWH + G::COLS) : G::COLS;
+    const int span = G::BWH + G::COLS;
     pf.fast = gx0 >= 4 && gx0 + span + 8 <= W;
     if (!pf.fast) return;
     const int nd = (G::COLS * es + 6) / 4;
@@ -124,14 +126,14 @@ mf_obl_issue(const unsigned char* __restrict__ src, int H, int W, long long pitc
     for (int u = 0; u < G::U; ++u) {
         const int it = tid + u * G::NT;
         pf.va[u] = 0;
-        if constexpr (G::PACK) pf.vb[u] = 0;
+        pf.vb[u] = 0;
         if (it < G::ROWS * nd) {
             const int rho = it / nd, d = it - rho * nd;
             const int gy = mf_clampi(Y0 - G::RV + rho, 0, H - 1);
             const uintptr_t a = (uintptr_t)(src + (long long)gy * pitch + (long long)gx0 * es);
             const uint32_t* p = (const uint32_t*)((a & ~(uintptr_t)3) + 4 * (uintptr_t)d);
             pf.va[u] = p[0];
-            if constexpr (G::PACK) pf.vb[u] = p[G::BWH * es / 4];
+            pf.vb[u] = p[G::BWH * es / 4];
         }
     }
 }
@@ -179,6 +181,82 @@ __device__ __forceinline__ void mf_obl_put_dword(V* __restrict__ rrow, int b0, u
     }
 }
 
+// Footprint union of 32-bit data -> LDS raw buffer. A wave takes every NW-th
+// footprint row: its address is scalar, and lane i loads the TW columns from
+// TW * i on (the first K - 1 lanes one of the last K - 1 columns besides), whose
+// places in the raw buffer are lane i's word of TW consecutive planes, without
+// bank conflicts and at compile-time offsets. Dword by dword, each with its own
+// row, column and address, the staging was 40 % of the k = 7 kernel's VALU
+// instructions, which bound it (float32 4096^2: k = 7 112 -> 71 us with the
+// stores by rows, k = 5 103 -> 58, k = 17 470 -> 445).
+template <class V, int K, int KH, int TW, int TH, int RY, int NW>
+__device__ __forceinline__ void
+mf_obl_load_rows(const unsigned char* __restrict__ src, int H, int W, long long pitch, int dtype, int X0, int Y0,
+                 V* __restrict__ raw)
+{
+    using G = MfObGeom<V, K, KH, TW, TH, RY, NW>;
+    constexpr int Q = G::Q, NR = (G::ROWS + NW - 1) / NW;
+    constexpr int VW = TW < 4 ? TW : 4;
+    typedef uint32_t vec __attribute__((ext_vector_type(VW), aligned(4)));
+    static_assert(!G::PACK && K <= 65 && TW % VW == 0, "a lane takes TW columns and at most one more");
+    const int tid = mf_tid();
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int gx0 = X0 - G::RX;
+    const bool tail = lane < K - 1;
+    uint32_t v[NR][TW], w[NR];
+    auto row = [&](int i) {            // rows past the last load it again
+        const int gy = mf_clampi(Y0 - G::RV + min(wv + i * NW, G::ROWS - 1), 0, H - 1);
+        return (const uint32_t*)(src + (long long)gy * pitch);
+    };
+    if (gx0 >= 0 && gx0 + G::COLS <= W) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const uint32_t* r = row(i) + gx0;
+#pragma unroll
+            for (int e = 0; e < TW; e += VW) {
+                const vec q = *(const vec*)(r + (uint32_t)(lane * TW + e));
+#pragma unroll
+                for (int f = 0; f < VW; ++f) {
+                    if constexpr (VW == 1) v[i][e] = q[0];
+                    else v[i][e + f] = q[f];
+                }
+            }
+            w[i] = 0;
+            if (K > 1 && tail) w[i] = r[64u * TW + lane];
+        }
+    } else {
+        uint32_t x[TW];
+#pragma unroll
+        for (int e = 0; e < TW; ++e) x[e] = mf_clampi(gx0 + lane * TW + e, 0, W - 1);
+        const uint32_t xt = mf_clampi(gx0 + 64 * TW + lane, 0, W - 1);
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            const uint32_t* r = row(i);
+#pragma unroll
+            for (int e = 0; e < TW; ++e) v[i][e] = r[x[e]];
+            w[i] = 0;
+            if (K > 1 && tail) w[i] = r[xt];
+        }
+    }
+    if (dtype == MF_F32) {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+#pragma unroll
+            for (int e = 0; e < TW; ++e) v[i][e] = mf_f32_to_key(v[i][e]);
+            w[i] = mf_f32_to_key(w[i]);
+        }
+    }
+    V* p = raw + wv * TW * Q + lane;
+    V* pt = raw + (wv * TW + lane % TW) * Q + 64 + lane / TW;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        if ((i + 1) * NW > G::ROWS && wv + i * NW >= G::ROWS) break;
+#pragma unroll
+        for (int e = 0; e < TW; ++e) p[(i * NW * TW + e) * Q] = v[i][e];
+        if (K > 1 && tail) pt[i * NW * TW * Q] = w[i];
+    }
+}
+
 // Footprint union with clamped coordinates, element by element (blocks at
 // the left or right image edge).
 template <class V, int K, int KH, int TW, int TH, int RY, int NW>
@@ -187,21 +265,23 @@ mf_obl_load_clamped(const unsigned char* __restrict__ src, int H, int W, long lo
                     V* __restrict__ raw)
 {
     using G = MfObGeom<V, K, KH, TW, TH, RY, NW>;
-    constexpr int Q = G::Q, COLS = G::COLS;
-    constexpr int UC = (G::ROWS * COLS + G::NT - 1) / G::NT;
-    const int tid = mf_tid();
-    // unrolled: every load of the thread is in flight at once
+    if constexpr (!G::PACK) {
+        mf_obl_load_rows<V, K, KH, TW, TH, RY, NW>(src, H, W, pitch, dtype, X0, Y0, raw);
+    } else {
+        constexpr int Q = G::Q, COLS = G::COLS;
+        constexpr int UC = (G::ROWS * COLS + G::NT - 1) / G::NT;
+        const int tid = mf_tid();
+        // unrolled: every load of the thread is in flight at once
 #pragma unroll
-    for (int u = 0; u < UC; ++u) {
-        const int w = tid + u * G::NT;
-        if (w >= G::ROWS * COLS) break;
-        const int rho = w / COLS, c = w - rho * COLS;
-        const int gy = mf_clampi(Y0 - G::RV + rho, 0, H - 1);
-        const unsigned char* row = src + (long long)gy * pitch;
-        const int gxa = mf_clampi(X0 - G::RX + c, 0, W - 1);
-        V v;
-        if constexpr (G::PACK) {
+        for (int u = 0; u < UC; ++u) {
+            const int w = tid + u * G::NT;
+            if (w >= G::ROWS * COLS) break;
+            const int rho = w / COLS, c = w - rho * COLS;
+            const int gy = mf_clampi(Y0 - G::RV + rho, 0, H - 1);
+            const unsigned char* row = src + (long long)gy * pitch;
+            const int gxa = mf_clampi(X0 - G::RX + c, 0, W - 1);
             const int gxb = mf_clampi(X0 + G::BWH - G::RX + c, 0, W - 1);
+            V v;
             if (dtype == MF_U8) {
                 v.x = row[gxa];
                 v.y = row[gxb];
@@ -209,12 +289,8 @@ mf_obl_load_clamped(const unsigned char* __restrict__ src, int H, int W, long lo
                 v.x = ((const uint16_t*)row)[gxa];
                 v.y = ((const uint16_t*)row)[gxb];
             }
-        } else {
-            uint32_t b = ((const uint32_t*)row)[gxa];
-            if (dtype == MF_F32) b = mf_f32_to_key(b);
-            v = b;
+            raw[(rho * TW + c % TW) * Q + c / TW] = v;
         }
-        raw[(rho * TW + c % TW) * Q + c / TW] = v;
     }
 }
 
@@ -227,7 +303,7 @@ mf_obl_commit(const unsigned char* __restrict__ src, int H, int W, long long pit
 {
     using G = MfObGeom<V, K, KH, TW, TH, RY, NW>;
     constexpr int Q = G::Q, COLS = G::COLS;
-    const int es = G::PACK ? (dtype == MF_U8 ? 1 : 2) : 4;
+    const int es = dtype == MF_U8 ? 1 : 2;
     const int gx0 = X0 - G::RX;
     if (pf.fast) {
         const int nd = (COLS * es + 6) / 4;
@@ -240,8 +316,7 @@ mf_obl_commit(const unsigned char* __restrict__ src, int H, int W, long long pit
                 const int gy = mf_clampi(Y0 - G::RV + rho, 0, H - 1);
                 const uintptr_t a = (uintptr_t)(src + (long long)gy * pitch + (long long)gx0 * es);
                 const int lead = (int)(a & 3);            // bytes before the segment start
-                mf_obl_put_dword<V, K, KH, TW, TH, RY, NW>(raw + rho * TW * Q, 4 * d - lead, pf.va[u],
-                                                       G::PACK ? pf.vb[u] : 0u, es, dtype);
+                mf_obl_put_dword<V, K, KH, TW, TH, RY, NW>(raw + rho * TW * Q, 4 * d - lead, pf.va[u], pf.vb[u], es, dtype);
             }
         }
         return;
@@ -366,25 +441,91 @@ __device__ __forceinline__ void mf_obl_stage_commit(const uint4* stage, int dtyp
 }
 
 // Sorted column segments of every tile row (initialisation, shared by the
-// horizontally adjacent tiles of the row).
+// horizontally adjacent tiles of the row). Short segments: a wave sorts its own
+// tile rows' columns, lane i those of the TW planes at word i (as the networks
+// read them, no address arithmetic per segment), and the K - 1 columns right of
+// the last lane's go to the block's first threads. Long segments: all columns
+// in turn over the block's threads, since the last K - 1 would keep one wave
+// sorting while the others wait (uint8 k = 17, segments of 14: 1.42 against
+// 1.46 ms a 30 MP frame; k = 9, of 6: 399 against 392 us).
 template <class NET, class V, int RY, int NW>
 __device__ __forceinline__ void mf_obl_colsort(const V* __restrict__ raw, V* __restrict__ colb)
 {
     using G = MfObGeom<V, NET::K, NET::KH, NET::TW, NET::TH, RY, NW>;
-    constexpr int TW = NET::TW, TH = NET::TH, LC = NET::LC, Q = G::Q, COLS = G::COLS;
+    constexpr int TW = NET::TW, TH = NET::TH, LC = NET::LC, Q = G::Q, COLS = G::COLS, EX = NET::K - 1;
     const int tid = mf_tid();
-    // two column segments per thread in flight hide the LDS latency
+    if constexpr (LC > 8) {
+        // two column segments per thread in flight hide the LDS latency
 #pragma unroll 2
-    for (int it = tid; it < G::TY * COLS; it += G::NT) {
-        const int j = it / COLS, c = it - j * COLS;
-        V a[LC];
+        for (int it = tid; it < G::TY * COLS; it += G::NT) {
+            const int j = it / COLS, c = it - j * COLS;
+            V a[LC];
 #pragma unroll
-        for (int i = 0; i < LC; ++i)
-            a[i] = raw[((j * TH + TH - 1 + i) * TW + c % TW) * Q + c / TW];
-        NET::sort_column(a);
+            for (int i = 0; i < LC; ++i)
+                a[i] = raw[((j * TH + TH - 1 + i) * TW + c % TW) * Q + c / TW];
+            NET::sort_column(a);
 #pragma unroll
-        for (int i = 0; i < LC; ++i)
-            colb[((j * LC + i) * TW + c % TW) * Q + c / TW] = a[i];
+            for (int i = 0; i < LC; ++i)
+                colb[((j * LC + i) * TW + c % TW) * Q + c / TW] = a[i];
+        }
+    } else {
+        const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+        auto sort = [&](int j, int x) {      // x: place in a row of the buffers
+            V a[LC];
+#pragma unroll
+            for (int i = 0; i < LC; ++i) a[i] = raw[(j * TH + TH - 1 + i) * TW * Q + x];
+            NET::sort_column(a);
+#pragma unroll
+            for (int i = 0; i < LC; ++i) colb[(j * LC + i) * TW * Q + x] = a[i];
+        };
+        for (int ry = 0; ry < RY; ++ry) {
+#pragma unroll 2
+            for (int e = 0; e < TW; ++e) sort(wv * RY + ry, e * Q + lane);
+        }
+        if constexpr (EX > 0) {
+            for (int it = tid; it < G::TY * EX; it += G::NT) {
+                const int j = it / EX, c = it - j * EX;
+                sort(j, c % TW * Q + 64 + c / TW);
+            }
+        }
+    }
+}
+
+// TW adjacent medians (of each packed half, BWH columns apart) -> row y of the
+// image, one store where they are all inside it.
+template <class V, int TW, int BWH>
+__device__ __forceinline__ void mf_obl_store_row(const V (&m)[TW], unsigned char* __restrict__ dst, int H, int W,
+                                                 long long pitch, int dtype, int tx, int y)
+{
+    if (y >= H) return;
+    unsigned char* row = dst + (long long)y * pitch;
+    auto put = [&](const auto (&b)[TW], int x) {
+        auto* o = (std::remove_cv_t<std::remove_reference_t<decltype(b[0])>>*)row + x;
+        if (x + TW <= W) {
+            __builtin_memcpy(o, b, sizeof(b));
+        } else {
+#pragma unroll
+            for (int e = 0; e < TW; ++e)
+                if (x + e < W) o[e] = b[e];
+        }
+    };
+    if constexpr (!MfVTraits<V>::PACK) {
+        uint32_t b[TW];
+#pragma unroll
+        for (int e = 0; e < TW; ++e) b[e] = dtype == MF_F32 ? mf_key_to_f32(m[e]) : m[e];
+        put(b, tx);
+    } else if (dtype == MF_U8) {
+        unsigned char a[TW], b[TW];
+#pragma unroll
+        for (int e = 0; e < TW; ++e) a[e] = (unsigned char)m[e].x, b[e] = (unsigned char)m[e].y;
+        put(a, tx);
+        put(b, tx + BWH);
+    } else {
+        uint16_t a[TW], b[TW];
+#pragma unroll
+        for (int e = 0; e < TW; ++e) a[e] = m[e].x, b[e] = m[e].y;
+        put(a, tx);
+        put(b, tx + BWH);
     }
 }
 
@@ -401,7 +542,10 @@ mf_obl_networks(const V* __restrict__ raw, const V* __restrict__ colb, unsigned 
     constexpr bool PACK = G::PACK;
     constexpr int TW = NET::TW, TH = NET::TH, LC = NET::LC, Q = G::Q, BWH = G::BWH;
     const int tid = mf_tid();
-    const int lane = tid & 63, wv = tid >> 6;
+    // few medians: kept until the tile is done and stored by rows (uint16 k = 7
+    // 4096^2 86 -> 64 us with the column sorts above)
+    constexpr bool BY_ROWS = !OUT_LDS && TW > 1 && TW * TH <= 8;
+    const int lane = tid & 63, wv = BY_ROWS ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     for (int ry = 0; ry < RY; ++ry) {
         const int j = wv * RY + ry;
         const V* cb = colb + j * LC * TW * Q + lane;
@@ -428,7 +572,8 @@ mf_obl_networks(const V* __restrict__ raw, const V* __restrict__ colb, unsigned 
             NET::template run<Q>(cb, rb, sink);
         } else {
             const int ty = Y0 + j * TH, tx = X0 + lane * TW;
-            auto sink = [&](int px, int py, V v) {
+            // one median of the tile
+            auto put = [&](int px, int py, V v) {
                 const int y = ty + py;
                 if (y >= H) return;
                 unsigned char* row = dst + (long long)y * pitch;
@@ -446,7 +591,15 @@ mf_obl_networks(const V* __restrict__ raw, const V* __restrict__ colb, unsigned 
                     if (xa < W) ((uint32_t*)row)[xa] = (dtype == MF_F32) ? mf_key_to_f32(v) : v;
                 }
             };
-            NET::template run<Q>(cb, rb, sink);
+            if constexpr (BY_ROWS) {
+                V med[TH][TW];
+                auto sink = [&](int px, int py, V v) { med[py][px] = v; };
+                NET::template run<Q>(cb, rb, sink);
+#pragma unroll
+                for (int py = 0; py < TH; ++py) mf_obl_store_row<V, TW, BWH>(med[py], dst, H, W, pitch, dtype, tx, ty + py);
+            } else {
+                NET::template run<Q>(cb, rb, put);
+            }
         }
     }
 }
@@ -510,9 +663,13 @@ mf_obl_block(const unsigned char* __restrict__ src, unsigned char* __restrict__ 
     __shared__ V colb[NET::INLINE_COLS ? 1 : G::TY * NET::LC * NET::TW * G::Q];
     const int X0 = bx * (G::PACK ? 2 * G::BWH : G::BWH);
     const int Y0 = by * (G::TY * NET::TH);
-    MfObPrefetch<V, NET::K, NET::KH, NET::TW, NET::TH, RY, NW> pf;
-    mf_obl_issue(src, H, W, pitch, dtype, X0, Y0, pf);
-    mf_obl_commit(src, H, W, pitch, dtype, X0, Y0, pf, raw);
+    if constexpr (G::PACK) {
+        MfObPrefetch<V, NET::K, NET::KH, NET::TW, NET::TH, RY, NW> pf;
+        mf_obl_issue(src, H, W, pitch, dtype, X0, Y0, pf);
+        mf_obl_commit(src, H, W, pitch, dtype, X0, Y0, pf, raw);
+    } else {
+        mf_obl_load_rows<V, NET::K, NET::KH, NET::TW, NET::TH, RY, NW>(src, H, W, pitch, dtype, X0, Y0, raw);
+    }
     __syncthreads();
     if constexpr (!NET::INLINE_COLS) {
         mf_obl_colsort<NET, V, RY, NW>(raw, colb);
