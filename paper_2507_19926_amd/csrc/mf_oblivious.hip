@@ -81,12 +81,6 @@ struct MfObGeom {
     static constexpr int COLS = BWH + K - 1;       // footprint-union columns
     static constexpr int ROWS = TY * TH + KH - 1;  // footprint-union rows
     static constexpr int Q = (COLS + TW - 1) / TW;
-    // a segment of seg_bytes starting `lead` (< 4) bytes into an aligned
-    // dword needs ceil((lead + seg_bytes) / 4) <= (seg_bytes + 6) / 4 dwords;
-    // they end at most 6 bytes past the segment, inside the row because of
-    // the 8-element margin of the fast-path test
-    static constexpr int NDMAX = (COLS * (PACK ? 2 : 4) + 6) / 4;
-    static constexpr int U = (ROWS * NDMAX + NT - 1) / NT;
     // Staging buffer of the persistent form: every footprint row as whole
     // 16-byte chunks of the source row. A row needs the dwords the commit
     // reads, which end at most 18 bytes past SPAN elements from the first
@@ -96,47 +90,6 @@ struct MfObGeom {
     // whole 64-chunk groups: one wave instruction fills 64 consecutive chunks
     static constexpr int STG_CHUNKS = (ROWS * NCH + 63) / 64 * 64;
 };
-
-// Global loads of one block's footprint union (plain and batched forms,
-// packed types), issued all at once into registers, then scattered into LDS.
-template <class V, int K, int KH, int TW, int TH, int RY, int NW>
-struct MfObPrefetch {
-    using G = MfObGeom<V, K, KH, TW, TH, RY, NW>;
-    uint32_t va[G::U], vb[G::U];
-    bool fast;
-};
-
-// Blocks whose columns stay inside the image with an 8-element margin take
-// the fast path: aligned dword loads of whole row segments. Blocks touching
-// the left or right edge clamp element by element at commit time.
-template <class V, int K, int KH, int TW, int TH, int RY, int NW>
-__device__ __forceinline__ void
-mf_obl_issue(const unsigned char* __restrict__ src, int H, int W, long long pitch, int dtype, int X0, int Y0,
-             MfObPrefetch<V, K, KH, TW, TH, RY, NW>& pf)
-{
-    using G = MfObGeom<V, K, KH, TW, TH, RY, NW>;
-    const int es = dtype == MF_U8 ? 1 : 2;
-    const int gx0 = X0 - G::RX;
-    const int span = G::BWH + G::COLS;
-    pf.fast = gx0 >= 4 && gx0 + span + 8 <= W;
-    if (!pf.fast) return;
-    const int nd = (G::COLS * es + 6) / 4;
-    const int tid = mf_tid();
-#pragma unroll
-    for (int u = 0; u < G::U; ++u) {
-        const int it = tid + u * G::NT;
-        pf.va[u] = 0;
-        pf.vb[u] = 0;
-        if (it < G::ROWS * nd) {
-            const int rho = it / nd, d = it - rho * nd;
-            const int gy = mf_clampi(Y0 - G::RV + rho, 0, H - 1);
-            const uintptr_t a = (uintptr_t)(src + (long long)gy * pitch + (long long)gx0 * es);
-            const uint32_t* p = (const uint32_t*)((a & ~(uintptr_t)3) + 4 * (uintptr_t)d);
-            pf.va[u] = p[0];
-            pf.vb[u] = p[G::BWH * es / 4];
-        }
-    }
-}
 
 // Scatter the elements of one source dword into the raw buffer's row. b0 is
 // the footprint column of the dword's byte 0 (may be negative); vb is the
@@ -257,8 +210,9 @@ mf_obl_load_rows(const unsigned char* __restrict__ src, int H, int W, long long 
     }
 }
 
-// Footprint union with clamped coordinates, element by element (blocks at
-// the left or right image edge).
+// Footprint union with clamped coordinates, element by element for packed data
+// (the persistent form's blocks that cannot be staged: mf_obl_load_packed there
+// costs the network's registers, uint16 k = 17 1.6 % on 30 MP).
 template <class V, int K, int KH, int TW, int TH, int RY, int NW>
 __device__ __forceinline__ void
 mf_obl_load_clamped(const unsigned char* __restrict__ src, int H, int W, long long pitch, int dtype, int X0, int Y0,
@@ -294,34 +248,89 @@ mf_obl_load_clamped(const unsigned char* __restrict__ src, int H, int W, long lo
     }
 }
 
-// Footprint union -> LDS raw buffer (swizzled layout), from the prefetched
-// registers or, for edge blocks, by clamped element loads.
-template <class V, int K, int KH, int TW, int TH, int RY, int NW>
+// Footprint union of 8- or 16-bit data -> LDS raw buffer (swizzled layout), rows
+// and columns shared out as by mf_obl_load_rows: a lane loads its columns of each
+// half in one piece, at whatever address. Before, each dword of the rows was
+// scattered by element, with an address and two bounds checks for each (4096^2
+// uint16: k = 5 58 -> 34 us, k = 7 64 -> 49, k = 11 125 -> 92; 8-bit data alike).
+template <class V, class T, int K, int KH, int TW, int TH, int RY, int NW>
 __device__ __forceinline__ void
-mf_obl_commit(const unsigned char* __restrict__ src, int H, int W, long long pitch, int dtype, int X0, int Y0,
-              const MfObPrefetch<V, K, KH, TW, TH, RY, NW>& pf, V* __restrict__ raw)
+mf_obl_load_packed(const unsigned char* __restrict__ src, int H, int W, long long pitch, int X0, int Y0,
+                   V* __restrict__ raw)
 {
     using G = MfObGeom<V, K, KH, TW, TH, RY, NW>;
-    constexpr int Q = G::Q, COLS = G::COLS;
-    const int es = dtype == MF_U8 ? 1 : 2;
+    constexpr int Q = G::Q, NR = (G::ROWS + NW - 1) / NW;
+    constexpr int PER = 4 / (int)sizeof(T), BITS = 8 * (int)sizeof(T);
+    constexpr int NWD = (TW + PER - 1) / PER;              // dwords of a lane's columns
+    static_assert(G::PACK && K <= 65, "a lane takes TW columns and at most one more");
+    const int tid = mf_tid();
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int gx0 = X0 - G::RX;
-    if (pf.fast) {
-        const int nd = (COLS * es + 6) / 4;
-        const int tid = mf_tid();
+    const bool tail = lane < K - 1;
+    auto row = [&](int i) {            // rows past the last load it again
+        const int gy = mf_clampi(Y0 - G::RV + min(wv + i * NW, G::ROWS - 1), 0, H - 1);
+        return (const T*)(src + (long long)gy * pitch);
+    };
+    auto value = [&](const uint32_t (&b)[2]) {
+        V v;
+        v.x = (unsigned short)b[0];
+        v.y = (unsigned short)b[1];
+        return v;
+    };
+    V* p = raw + wv * TW * Q + lane;
+    V* pt = raw + (wv * TW + lane % TW) * Q + 64 + lane / TW;
+    auto past = [&](int i) { return (i + 1) * NW > G::ROWS && wv + i * NW >= G::ROWS; };
+    uint32_t t[NR][2];
+    if (gx0 >= 0 && gx0 + G::BWH + G::COLS <= W) {
+        uint32_t w[NR][2][NWD];
 #pragma unroll
-        for (int u = 0; u < G::U; ++u) {
-            const int it = tid + u * G::NT;
-            if (it < G::ROWS * nd) {
-                const int rho = it / nd, d = it - rho * nd;
-                const int gy = mf_clampi(Y0 - G::RV + rho, 0, H - 1);
-                const uintptr_t a = (uintptr_t)(src + (long long)gy * pitch + (long long)gx0 * es);
-                const int lead = (int)(a & 3);            // bytes before the segment start
-                mf_obl_put_dword<V, K, KH, TW, TH, RY, NW>(raw + rho * TW * Q, 4 * d - lead, pf.va[u], pf.vb[u], es, dtype);
+        for (int i = 0; i < NR; ++i) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const T* r = row(i) + gx0 + h * G::BWH;
+                w[i][h][0] = t[i][h] = 0;
+                __builtin_memcpy(w[i][h], r + (uint32_t)(lane * TW), TW * sizeof(T));
+                if (K > 1 && tail) t[i][h] = r[64u * TW + lane];
             }
         }
-        return;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            if (past(i)) break;
+#pragma unroll
+            for (int e = 0; e < TW; ++e) {
+                uint32_t b[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    b[h] = w[i][h][e / PER] >> (e % PER * BITS) & ((1u << BITS) - 1);
+                p[(i * NW * TW + e) * Q] = value(b);
+            }
+            if (K > 1 && tail) pt[i * NW * TW * Q] = value(t[i]);
+        }
+    } else {
+        uint32_t v[NR][TW][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint32_t x[TW];
+#pragma unroll
+            for (int e = 0; e < TW; ++e) x[e] = mf_clampi(gx0 + h * G::BWH + lane * TW + e, 0, W - 1);
+            const uint32_t xt = mf_clampi(gx0 + h * G::BWH + 64 * TW + lane, 0, W - 1);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const T* r = row(i);
+#pragma unroll
+                for (int e = 0; e < TW; ++e) v[i][e][h] = r[x[e]];
+                t[i][h] = 0;
+                if (K > 1 && tail) t[i][h] = r[xt];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            if (past(i)) break;
+#pragma unroll
+            for (int e = 0; e < TW; ++e) p[(i * NW * TW + e) * Q] = value(v[i][e]);
+            if (K > 1 && tail) pt[i * NW * TW * Q] = value(t[i]);
+        }
     }
-    mf_obl_load_clamped<V, K, KH, TW, TH, RY, NW>(src, H, W, pitch, dtype, X0, Y0, raw);
 }
 
 // Persistent form, stage 1a: start copying the footprint union of block
@@ -414,10 +423,9 @@ __device__ __forceinline__ void mf_obl_stage_commit_clamped(const uint4* stage, 
 }
 
 // Persistent form, stage 1b: staging buffer -> raw buffer (swizzled, packed
-// layout). Reads the same dwords as the register path: dword d of row rho
-// starts at footprint column 4d - lead, at staging byte (gx0*es mod 16) rounded
-// down to 4, plus 4d (+ BWH*es for the right half); the last byte read is below
-// 12 + 4*nd + BWH*es <= 18 + SPAN*es, inside the row's nch chunks.
+// layout). Dword d of row rho starts at footprint column 4d - lead, at staging
+// byte (gx0*es mod 16) rounded down to 4, plus 4d (+ BWH*es for the right
+// half); the last byte read is below 12 + 4*nd + BWH*es <= 18 + SPAN*es, inside the row's nch chunks.
 template <class V, int K, int KH, int TW, int TH, int RY, int NW>
 __device__ __forceinline__ void mf_obl_stage_commit(const uint4* stage, int dtype, int X0, V* __restrict__ raw)
 {
@@ -663,13 +671,12 @@ mf_obl_block(const unsigned char* __restrict__ src, unsigned char* __restrict__ 
     __shared__ V colb[NET::INLINE_COLS ? 1 : G::TY * NET::LC * NET::TW * G::Q];
     const int X0 = bx * (G::PACK ? 2 * G::BWH : G::BWH);
     const int Y0 = by * (G::TY * NET::TH);
-    if constexpr (G::PACK) {
-        MfObPrefetch<V, NET::K, NET::KH, NET::TW, NET::TH, RY, NW> pf;
-        mf_obl_issue(src, H, W, pitch, dtype, X0, Y0, pf);
-        mf_obl_commit(src, H, W, pitch, dtype, X0, Y0, pf, raw);
-    } else {
+    if constexpr (!G::PACK)
         mf_obl_load_rows<V, NET::K, NET::KH, NET::TW, NET::TH, RY, NW>(src, H, W, pitch, dtype, X0, Y0, raw);
-    }
+    else if (dtype == MF_U8)
+        mf_obl_load_packed<V, uint8_t, NET::K, NET::KH, NET::TW, NET::TH, RY, NW>(src, H, W, pitch, X0, Y0, raw);
+    else
+        mf_obl_load_packed<V, uint16_t, NET::K, NET::KH, NET::TW, NET::TH, RY, NW>(src, H, W, pitch, X0, Y0, raw);
     __syncthreads();
     if constexpr (!NET::INLINE_COLS) {
         mf_obl_colsort<NET, V, RY, NW>(raw, colb);
