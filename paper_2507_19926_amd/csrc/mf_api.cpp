@@ -137,7 +137,8 @@ bool hist_is_faster(int32_t dtype, int32_t k)
 }
 
 // What a call of `pixels` pixels runs instead of the choice for large images
-// when it is small: a network's wave takes its 20-70 us (k = 9 to 21) and a
+// when it is small (network: 8-bit images of a batch, see
+// mf_internal_small_batch): a network's wave takes its 20-70 us (k = 9 to 21) and a
 // ranked region its 40-120 us however few there are, while a schedule's time
 // falls with the pixels and the 8-bit histograms start at 11 us. us, one plane
 // of uniform noise (normal float32), network / schedule / histograms:
@@ -147,7 +148,7 @@ bool hist_is_faster(int32_t dtype, int32_t k)
 //           k = 23  320^2 - / 33 / 44, 384^2 - / 50 / 43;  k = 75  256^2 - / 67 / 78
 //   float32 k = 17  256^2 32 / 22, 384^2 32 / 58;  k = 19  256^2 47 / 21, 384^2 47 / 57
 //           k = 23  320^2 - / 52 / 66, 384^2 - / 73 / 66
-enum class Small { no, schedule, histograms };
+enum class Small { no, schedule, network, histograms };
 Small small_choice(int32_t dtype, int32_t k, int64_t pixels)
 {
     if (dtype == MF_U8)
@@ -306,23 +307,33 @@ int32_t mf_internal_validate(const void* src, const void* dst, int64_t H, int64_
 
 int32_t mf_internal_fail(int32_t code, const char* msg) { return fail(code, "%s", msg); }
 
-// Whether the images of a batch that would be ranked are together too few.
-bool mf_internal_small_batch(const mf_image* imgs, int32_t n)
+// Which images of a batch are together too few for their histograms: 1, those
+// that would be ranked (below 2^19 pixels: a batched region has 64 rows and takes
+// 75-105 us alone), 2, the 8-bit ones that have a network (below 2^20: each
+// window's histograms are one more kernel of the graph, the networks are shared
+// with the 16-bit images). Batches, with histograms for 8-bit data always and
+// ranks from 2^17 pixels, against these lines: 16 images of up to 512 a side 282
+// / 204 us, 24 305 / 186, 31 of up to 280 176 / 132, 74 of up to 1195 161 / 130;
+// 73 of up to 1197 and 164 of up to 824 the same.
+int mf_internal_small_batch(const mf_image* imgs, int32_t n)
 {
-    int64_t px = 0;
-    for (int i = 0; i < n && px < (1 << 17); ++i)
-        if (imgs[i].dtype != MF_U8 && hist_is_faster(imgs[i].dtype, imgs[i].k))
-            px += pixels_of(1, imgs[i].H, imgs[i].W);
-    return px < (1 << 17);
+    int64_t wide = 0, bytes = 0;
+    for (int i = 0; i < n && (wide < (1 << 19) || bytes < (1 << 20)); ++i) {
+        if (!hist_is_faster(imgs[i].dtype, imgs[i].k)) continue;
+        if (imgs[i].dtype != MF_U8) wide += pixels_of(1, imgs[i].H, imgs[i].W);
+        else if (imgs[i].k <= 21) bytes += pixels_of(1, imgs[i].H, imgs[i].W);
+    }
+    return (wide < (1 << 19) ? 1 : 0) | (bytes < (1 << 20) ? 2 : 0);
 }
 
 int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t* tw, int32_t* th,
                             int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form,
-                            bool small)
+                            int small)
 {
     const OblEntry* e = nullptr;
+    const bool few = dtype == MF_U8 ? (small & 2) && k <= 21 : (small & 1) != 0;
     int32_t rc = resolve(dtype, k, nullptr, variant, tw, th, &e, group, da_form,
-                         small && dtype != MF_U8 && hist_is_faster(dtype, k) ? Small::schedule : Small::no);
+                         !few || !hist_is_faster(dtype, k) ? Small::no : dtype == MF_U8 ? Small::network : Small::schedule);
     if (rc) return rc;
     // the column-strip form has no batched kernel: plans use k's default
     // network
@@ -434,9 +445,12 @@ int32_t median_filter_rect(const void* src, void* dst, int64_t planes, int64_t p
     if (!mf_da_supports(dtype, kw, 0, 0, 0, kh))
         return fail(MF_ERR_CONFIG, "no data-aware schedule for the %dx%d window", kw, kh);
     // without a network: sliding histograms instead of the schedule (30 MP RGB
-    // 8-bit frame: 21x13 0.45 ms against 9.9, 31x29 0.87 against 22 on noise)
+    // 8-bit frame: 21x13 0.45 ms against 9.9, 31x29 0.87 against 22 on noise).
+    // Ranked planes start at the line of small_choice(), windows of few values,
+    // which the schedule does faster, later (float32 11x21, 145 000 pixels 40 us
+    // against 63; 9x25, 539 000 117 against 74; 25x13, 198 000 76 against 59)
     if (variant == MF_VARIANT_AUTO && mf_hist_supports(dtype, kw, kh) &&
-        (dtype == MF_U8 || pixels_of(planes, H, W) >= (1 << 17)))   // the line of small_choice()
+        (dtype == MF_U8 || pixels_of(planes, H, W) >= (kw * kh < 300 ? 1 << 18 : 1 << 17)))
         return hip_status(mf_hist_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, dtype,
                                          kw, kh, (hipStream_t)stream),
                           "sliding-histogram kernel launch");
@@ -776,9 +790,12 @@ int32_t median_filter_3d(const void* src, void* dst, int64_t D, int64_t H, int64
         return MF_OK;
     }
     // 8-bit volumes slide histograms for every k (256^3, uniform noise, against
-    // the schedule: k = 3 0.44 ms against 1.10, k = 5 0.45 against 2.14, k = 9
-    // 0.54 against 4.61)
-    if (mf_hist3_supports(dtype, k))
+    // the schedule: k = 3 0.42 ms against 1.10, k = 5 0.38 against 2.14, k = 9
+    // 0.52 against 4.61) unless they are too narrow for a work-group's 128
+    // columns (128 x 128 x W, us: k = 3 W = 52 98 against 74, W = 70 98 against
+    // 138; k = 5 W = 8 53 against 26, W = 32 58 against 76; k = 7 W = 8 64 against
+    // 38, W = 32 67 against 115)
+    if (mf_hist3_supports(dtype, k) && W > (k == 3 ? 64 : k == 5 ? 16 : 8))
         return hip_status(mf_hist3_launch(src, dst, (int)D, (int)H, (int)W, pitch_bytes, slice_bytes, k, st),
                           "3-D sliding-histogram kernel launch");
     return hip_status(mf_da3_launch(src, dst, (int)D, (int)H, (int)W, pitch_bytes, slice_bytes, dtype, k, st),

@@ -25,8 +25,8 @@
 int32_t mf_internal_fail(int32_t code, const char* msg);
 int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t* tw, int32_t* th,
                             int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form,
-                            bool small);
-bool mf_internal_small_batch(const mf_image* imgs, int32_t n);
+                            int small);
+int mf_internal_small_batch(const mf_image* imgs, int32_t n);
 int32_t mf_internal_check_images(const mf_image* imgs, int32_t n);
 void mf_internal_batched_grids(int n, const MfBatchedKernel* kern, const long long* blocks, const int* k,
                                 unsigned* grid);
@@ -103,7 +103,7 @@ extern "C" int32_t median_filter_batched_noalloc(const mf_image* imgs, int32_t n
     }
     MfJob* const base = g_ptr[dev];
     // group the images by kernel, in first-appearance order
-    const bool small = mf_internal_small_batch(imgs, n);
+    const int small = mf_internal_small_batch(imgs, n);
     int nb = 0;
     for (int i = 0; i < n; ++i) {
         const mf_image& m = imgs[i];

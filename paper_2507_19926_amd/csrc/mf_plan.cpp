@@ -29,8 +29,8 @@ int32_t mf_internal_validate(const void* src, const void* dst, int64_t H, int64_
 int32_t mf_internal_fail(int32_t code, const char* msg);
 int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t* tw, int32_t* th,
                             int32_t* group, MfBatchedKernel* obl_p16, MfBatchedKernel* obl_u32, int32_t* da_form,
-                            bool small);
-bool mf_internal_small_batch(const mf_image* imgs, int32_t n);
+                            int small);
+int mf_internal_small_batch(const mf_image* imgs, int32_t n);
 
 namespace {
 
@@ -177,7 +177,7 @@ int32_t mf_plan_create(const mf_image* imgs, int32_t n, mf_plan* out)
         return hip_fail(e, "hipGetDevice");
     }
     // bucket by kernel
-    const bool small = mf_internal_small_batch(imgs, n);
+    const int small = mf_internal_small_batch(imgs, n);
     std::map<std::tuple<int, int, int, int, int>, int> index;
     for (int i = 0; i < n; ++i) {
         const mf_image& m = imgs[i];

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2507_19926_amd import workloads as wl
-from paper_2507_19926_amd.ops import median_filter, median_filter_rect
+from paper_2507_19926_amd.ops import BatchedPlan, median_filter, median_filter_3d, median_filter_rect
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +51,28 @@ def test_strips_of_either_chunk():
         img = wl.uniform_plane(H, 2048, np.uint8, seed=H)
         got = median_filter(torch.from_numpy(img).cuda(), 3).cpu().numpy()
         assert np.array_equal(got, oracle.median_filter(img, 3))
+
+
+@pytest.mark.parametrize("k,line", [(3, 64), (5, 16), (7, 8), (9, 8)])
+def test_narrow_volumes(k, line):
+    for W in (line, line + 1):
+        vol = wl.uniform_plane(6 * 9, W, np.uint8, seed=W).reshape(6, 9, W)
+        got = median_filter_3d(torch.from_numpy(vol).cuda(), k).cpu().numpy()
+        assert np.array_equal(got, oracle.median_filter_3d(vol, k)), W
+
+
+@pytest.mark.parametrize("dtype,k,line", [(np.uint8, 13, 1 << 20), (np.uint8, 21, 1 << 20), (np.uint8, 23, 1 << 20),
+                                          (np.uint16, 23, 1 << 19), (np.float32, 21, 1 << 19)])
+def test_batches_at_a_line(dtype, k, line):
+    """Two images whose pixels are together just below and at the line."""
+    for H in (line // 1024 - 33, line // 1024 - 32):
+        imgs = [_img(dtype, H, 1024, seed=k), _img(dtype, 32, 1024, seed=k + 1)]
+        xs = [torch.from_numpy(a).cuda() for a in imgs]
+        outs = [torch.empty_like(x) for x in xs]
+        plan = BatchedPlan(xs, outs, [k, k])
+        plan.launch()
+        g = np.random.default_rng(k)
+        for a, o in zip(imgs, outs):
+            ys, xx = g.integers(0, a.shape[0], 2000), g.integers(0, 1024, 2000)
+            assert o.cpu().numpy()[ys, xx].tobytes() == oracle.median_points(a, k, ys, xx).tobytes(), (H, a.shape)
+        plan.close()
