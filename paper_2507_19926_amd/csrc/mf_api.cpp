@@ -142,7 +142,7 @@ bool hist_is_faster(int32_t dtype, int32_t k)
 // ranked region its 40-120 us however few there are, while a schedule's time
 // falls with the pixels and the 8-bit histograms start at 11 us. us, one plane
 // of uniform noise (normal float32), network / schedule / histograms:
-//   uint8   k = 9   512^2 18 / 628 / 13;  k = 11 1024^2 23 / 1642 / 19
+//   uint8   k = 9   512^2 13.2 / 628 / 12.4;  k = 11  512^2 18.1 / - / 12.4, 724^2 18.1 / - / 18.6
 //   uint16  k = 17  384^2 37 / 28, 512^2 37 / 40;  k = 19  512^2 51 / 40, 768^2 52 / 74
 //           k = 21  256^2 68 / 24 / 42, 768^2 69 / 114 / 50, 1000x700 83 / 145 / 61
 //           k = 23  320^2 - / 33 / 44, 384^2 - / 50 / 43;  k = 75  256^2 - / 67 / 78
@@ -152,7 +152,7 @@ enum class Small { no, schedule, network, histograms };
 Small small_choice(int32_t dtype, int32_t k, int64_t pixels)
 {
     if (dtype == MF_U8)
-        return (k == 9 && pixels <= (1 << 18)) || (k == 11 && pixels <= (1 << 20)) ? Small::histograms : Small::no;
+        return (k == 9 && pixels <= (1 << 18)) || (k == 11 && pixels <= (3 << 17)) ? Small::histograms : Small::no;
     if (pixels < (1 << 17) && hist_is_faster(dtype, k)) return Small::schedule;
     if (dtype == MF_U16) {
         if (k == 17) return pixels <= (1 << 17) ? Small::schedule : Small::no;
