@@ -40,6 +40,9 @@
 
 #include "mf_hist.h"
 
+#define MF_HOST_DEVICE __host__ __device__
+#include "mf_hist_role.h"
+
 namespace {
 
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
@@ -167,8 +170,8 @@ struct Hist {
     // now; k = 17 1005 (1620), 940 (1390); k = 35 1430 (1560), 1270 (1390);
     // k = 65 2010, 1970; k = 75 2270, 2370, so the widest windows keep the wave
     // numbers, and the boxes beyond 9 (k = 15 1.71 ms, 1.75).
-    // Only the speed rests on what the registers say: unless the four waves
-    // are on four SIMDs, roles go by wave number.
+    // Only the speed rests on what the registers say: every wave takes its role
+    // from the same four published words, whose roles always differ.
     static constexpr bool kBySimd = P == 2 && (Z == 1 ? KW <= 67 : Z <= 9);
     static __device__ __forceinline__ int role()
     {
@@ -176,14 +179,13 @@ struct Hist {
         if constexpr (kBySimd) {
             constexpr int kSimd = 4 | 4 << 6 | 1 << 11;          // HW_ID bits 4..5
             constexpr int kLdsBase = 6 | 0 << 6 | 11 << 11;      // LDS_ALLOC bits 0..11
-            const uint32_t simd = __builtin_amdgcn_s_getreg(kSimd);
-            const uint32_t upper = __builtin_amdgcn_s_getreg(kLdsBase) != 0 ? 2u : 0u;
-            if (__lane_id() == 0) *(lds_u32*)(uintptr_t)(kStage + 4 * wave) = 1u << simd;
+            const uint32_t word = hist_role_word(__builtin_amdgcn_s_getreg(kSimd), __builtin_amdgcn_s_getreg(kLdsBase));
+            if (__lane_id() == 0) *(lds_u32*)(uintptr_t)(kStage + 4 * wave) = word;
             __syncthreads();
-            uint32_t all = 0;
-            for (int i = 0; i < 4; ++i) all |= *(const lds_u32*)(uintptr_t)(kStage + 4 * i);
-            if (__builtin_amdgcn_readfirstlane((int)all) == 15) wave = (int)(simd ^ upper);
-            wave = __builtin_amdgcn_readfirstlane(wave);
+            uint32_t words[4];
+            for (int i = 0; i < 4; ++i)
+                words[i] = __builtin_amdgcn_readfirstlane((int)*(const lds_u32*)(uintptr_t)(kStage + 4 * i));
+            wave = __builtin_amdgcn_readfirstlane(hist_role(words, wave));
             __syncthreads();
         }
         return wave;
