@@ -53,7 +53,10 @@ typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) u32x4a4 lds_u32x4a4;
 
 constexpr int kT = 4;                 // output columns of a group
-constexpr uint32_t kPad = 1024;       // the search may read three counters past either end
+// Room before the counters and after them: a lane whose median is found reads
+// on with the lanes that still walk, eight bins from its own each time, so
+// up to seven bins past either end. What it reads there is not used.
+constexpr uint32_t kPad = 2048;
 constexpr uint32_t kCounters = 65536;
 constexpr uint32_t kStage = kPad + kCounters + kPad;
 
