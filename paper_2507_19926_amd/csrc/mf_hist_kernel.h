@@ -75,8 +75,21 @@ struct Hist {
     static constexpr int NL = (kRow + 63) / 64;         // byte loads of a whole row
     static constexpr int NF = P == 1 ? (kRow + 127) / 128 : NL;   // of a wave's part of a row
     static constexpr int CH = (ND + 1) / 2 * 4;         // columns of the first half of a row
-    // staged rows: [2 steps][in, out][Z slices]; the first window takes them four at a time
-    static constexpr uint32_t kLds = kStage + 4 * Z * kRow;
+    // staged rows: [2 steps][in, out][Z slices]; the first window takes them four
+    // at a time. They hold whole loads, so that a store needs no condition (30 MP
+    // k = 17, smooth 208 us with conditions, 198 without)
+    static constexpr int kStaged = P == 1 ? 128 * NF : 64 * NL;
+    static constexpr uint32_t kRowsEnd = kStage + 4 * Z * kStaged;
+    // planes: counters of 16 bins each, as the bins' own at 256 v + 128 p + 4 g;
+    // a word in which a search wave asks for them, and one in which each says
+    // whether to go on with them
+    static constexpr bool kCoarse = Z == 1;
+    static constexpr uint32_t kAsk = kRowsEnd + 16 * 256;
+    static constexpr uint32_t kKeep = kAsk + 16;
+    static constexpr uint32_t kLds = kCoarse ? kKeep + 16 : kRowsEnd;
+    static_assert(kLds <= 80 * 1024, "two work-groups to a CU");
+    static constexpr int kFar = 4;       // probes of eight bins a row from which the counters of 16 bins pay
+    static constexpr int kFarRows = 16;  // rows for which they are kept at least
 
     // Column i of a group adds 1 << shift(i) to word(i).
     static constexpr int word(int i) { return P == 2 && (i == 2 || i >= KW); }
@@ -143,24 +156,97 @@ struct Hist {
     }
 
     // Adds one (or removes: one = -1) for the bytes of columns [C0, C1) of
-    // the group in R rows. With SYNC, the addresses are formed before a
-    // work-group barrier and the counters change after it.
-    template <int C0, int C1, bool SYNC, int R>
+    // the group in R rows, with COARSE to the counters of 16 bins too. With
+    // SYNC, the addresses are formed before a work-group barrier and the
+    // counters change after it.
+    template <int C0, int C1, bool SYNC, bool COARSE, int R>
     static __device__ __forceinline__ void update(const uint32_t (&d)[R][ND], uint32_t g4, int one)
     {
-        uint32_t a[R][C1 - C0];
+        uint32_t a[R][C1 - C0], c[C1 - C0];
+        auto at = [&](uint32_t q, int i) {
+            return __builtin_amdgcn_perm(q, word(i) ? g4 | 128u : g4, 0x0c0c0000u | ((4u + (i & 3)) << 8));
+        };
+        auto add = [&](uint32_t loc, int i) {
+            __hip_atomic_fetch_add((lds_u32*)(uintptr_t)loc, (uint32_t)one << shift(i), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int i = C0; i < C1; ++i)
-                a[r][i - C0] = __builtin_amdgcn_perm(d[r][i / 4], word(i) ? g4 | 128u : g4, 0x0c0c0000u | ((4u + (i & 3)) << 8));
+            for (int i = C0; i < C1; ++i) a[r][i - C0] = at(d[r][i / 4], i);
+        if constexpr (COARSE) {
+#pragma unroll
+            for (int i = C0; i < C1; ++i) c[i - C0] = at((d[0][i / 4] >> 4) & 0x0f0f0f0fu, i);
+        }
+        if constexpr (COARSE) {
+            // not sunk past the barrier
+#pragma unroll
+            for (int i = C0; i < C1; ++i) asm volatile("" : "+v"(a[0][i - C0]), "+v"(c[i - C0]));
+        }
         if (SYNC) __syncthreads();
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int i = C0; i < C1; ++i)
-                __hip_atomic_fetch_add((lds_u32*)(uintptr_t)(a[r][i - C0] + kPad), (uint32_t)one << shift(i),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (int i = C0; i < C1; ++i) add(a[r][i - C0] + kPad, i);
+        if constexpr (COARSE) {
+#pragma unroll
+            for (int i = C0; i < C1; ++i) add(c[i - C0] + kRowsEnd, i);
+        }
+    }
+
+    // The row steps of [y0, y1) by twos, for all waves alike. near(y) does steps
+    // y and y + 1 and returns whether a search wave has asked for the counters
+    // of 16 bins; far(y) does them with those; keep(n) leaves a search wave's
+    // word on the last n rows.
+    //
+    // The walk from one row's median to the next takes a probe for eight bins,
+    // up to 31 of 490 clocks on images of two levels, where a network's time
+    // does not depend on the data. With the counters of 16 bins a search reads
+    // 16 counters twice, whatever the data, but every row's updates and searches
+    // are longer, so they are kept only while the walks are long. A plane of
+    // 4480 x 6720 of two levels, us by walks alone / now (network): k = 13 1840 /
+    // 277 (325), k = 15 1866 / 294 (399), k = 17 2740 / 471 (495), k = 21 2756 / 494
+    // (1226). The question itself costs a smooth image 2 to 5 % of its time (k = 21
+    // 12 %, 193 / 217); asking every 16 rows, by a barrier of its own, cost as
+    // much, since the rows on their way to the registers are waited for there.
+    //
+    // The counters of 16 bins are summed from the bins' own where they begin: a
+    // field of a counter word over all 256 bins holds no more than a column's or
+    // the shared columns' values, so words of any bins add up without a carry.
+    //
+    // The word kAsk is written before the first barrier of step y + 1 and read by
+    // all waves before the second, and cleared after one more: all waves go the
+    // same way.
+    template <class Near, class Far, class Keep>
+    static __device__ __forceinline__ void rows(int y0, int y1, int wave, int lane, const Near& near, const Far& far,
+                                                const Keep& keep)
+    {
+        for (int y = y0;;) {
+            bool ask;
+            do {
+                ask = near(y);
+                y += 2;
+            } while (y < y1 && !ask);
+            if (!kCoarse || y >= y1) return;
+            for (int c = wave; c < 16; c += 2 * kWaves) {
+                const uint32_t a = kPad + (uint32_t)(c * 16 * 256 + 4 * lane);
+                uint32_t sum = 0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum += *(const lds_u32*)(uintptr_t)(a + 256 * i);
+                *(lds_u32*)(uintptr_t)(kRowsEnd + (uint32_t)(c * 256 + 4 * lane)) = sum;
+            }
+            __syncthreads();
+            if (wave == 0 && lane == 0) *(lds_u32*)(uintptr_t)kAsk = 0;
+            u32x4 on;
+            do {
+                const int begin = y, end = min(y + kFarRows, y1);
+                for (; y < end; y += 2) far(y);
+                if (y >= y1) return;
+                keep(y - begin);
+                __syncthreads();
+                on = *(const lds_u32x4*)(uintptr_t)kKeep;
+            } while (__builtin_amdgcn_readfirstlane((int)(on.x | on.y | on.z | on.w)) != 0);
+        }
     }
 
     // The wave's number among search (0 .. kWaves - 1) and slide waves. With
@@ -204,6 +290,10 @@ struct Hist {
         const int wave = role();
         for (uint32_t i = threadIdx.x * 16; i < kStage; i += kThreads * 16)
             *(lds_u32x4*)(uintptr_t)i = u32x4{0, 0, 0, 0};
+        if (kCoarse && threadIdx.x == 0) {
+            *(lds_u32*)(uintptr_t)kAsk = 0;
+            *(lds_u32x4*)(uintptr_t)kKeep = u32x4{0, 0, 0, 0};
+        }
         // row y of the q-th slice of the box
         auto row = [&](int y, int q) {
             const unsigned char* p = src + (long long)min(max(y, 0), H - 1) * pitch;
@@ -213,39 +303,66 @@ struct Hist {
         else slide(row, W, x0, y0, y1, kh, wave - kWaves, lane);
     }
 
+    // N counters from address a on, st apart, against the n values of the window
+    // that are to be passed: the number of counters passed (N: all), n becomes
+    // the rest and hi the complement of the values of the first counter not
+    // passed that rank above.
+    template <int N>
+    static __device__ __forceinline__ int probe(uint32_t a, int st, int w, int& n, uint32_t& hi)
+    {
+        int v[N];
+        bins<N>(v, a, st, w);
+        uint32_t lo = (uint32_t)n;
+        hi = 0;
+        int c = N, r = n;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            r -= v[i];
+            lo = min(lo, (uint32_t)r);
+            hi = max(hi, (uint32_t)r);
+            c += r >> 31;
+        }
+        n = (int)lo;
+        return c;
+    }
+
     // Next median of a lane: e = rank of the median - number of window values
     // below bin m, am = address of bin m; both move to the median's bin.
-    // Returns the number of window values of that bin that rank above.
-    static __device__ __forceinline__ int find(uint32_t& am, int& e, int w)
+    // Returns the number of window values of that bin that rank above; more
+    // counts the probes after the first.
+    static __device__ __forceinline__ int find(uint32_t& am, int& e, int w, int& more)
     {
         const int sg = e >> 31;
         const int st = sg ? -256 : 256;
         uint32_t a = am + (uint32_t)(sg & -256);
         int n = e ^ sg;
         uint32_t hi;
-        auto probe = [&](auto cnt) {
-            constexpr int N = decltype(cnt)::value;
-            int v[N];
-            bins<N>(v, a, st, w);
-            uint32_t lo = (uint32_t)n;
-            hi = 0;
-            int c = N, r = n;
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                r -= v[i];
-                lo = min(lo, (uint32_t)r);
-                hi = max(hi, (uint32_t)r);
-                c += r >> 31;
-            }
-            a += (uint32_t)(st * c);
-            n = (int)lo;
-            return __any(c == N);
-        };
-        if (probe(std::integral_constant<int, 4>{}))
-            while (probe(std::integral_constant<int, 8>{})) {}
+        int c = probe<4>(a, st, w, n, hi);
+        a += (uint32_t)(st * c);
+        if (__any(c == 4))
+            do {
+                c = probe<8>(a, st, w, n, hi);
+                a += (uint32_t)(st * c);
+                ++more;
+            } while (__any(c == 8));
         am = a;
         e = sg ? (int)~hi : n;
         return sg ? n : (int)~hi;
+    }
+
+    // The same by the counters of 16 bins: rank = rank of the median in the
+    // window. more: about what find() would have probed, by two distances.
+    static __device__ __forceinline__ void find_coarse(uint32_t& am, int& e, int w, uint32_t g4, int rank, int& more)
+    {
+        uint32_t hi, a = kRowsEnd + g4;
+        int n = rank;
+        asm("" : "+v"(a));     // one base for all reads
+        a = kPad + g4 + ((uint32_t)probe<16>(a, 256, w, n, hi) << 12);
+        a += (uint32_t)probe<16>(a, 256, w, n, hi) << 8;
+        const int far = abs((int)(a - am)) >> 8;
+        more += (__any(far > 28) ? 4 : 0) + (__any(far > 124) ? 12 : 0);
+        am = a;
+        e = n;
     }
 
     template <class Row>
@@ -253,13 +370,16 @@ struct Hist {
                                                   int x0, int y0, int y1, int kh, int wave, int lane)
     {
         const int ry = kh / 2;
-        const uint32_t g4 = 4u * (uint32_t)(lane & (kGroups - 1));
         const int w = P == 1 ? wave : 2 * wave + (lane >> 5);
-        const uint32_t vo = (uint32_t)(x0 + (int)g4 + w);
+        const uint32_t vo = (uint32_t)(x0 + 4 * (lane & (kGroups - 1)) + w);
+        // lanes outside the image search with the last group inside: the windows
+        // of the columns they stand for are the last column's values alone,
+        // whose medians can jump where the image's do not
+        const uint32_t g4 = 4u * (uint32_t)(min(lane & (kGroups - 1), max(W - 1 - x0 - w, 0) >> 2) & (kGroups - 1));
         const bool inside = (int)vo < W;
         uint32_t m;
         {
-            const uint32_t xo = (uint32_t)min((int)vo, W - 1);
+            const uint32_t xo = (uint32_t)min(x0 + (int)g4 + w, W - 1);
             const uint32_t a = row(y0 - ry, Z / 2)[xo], b = row(y0, Z / 2)[xo], c = row(y0 + ry, Z / 2)[xo];
             m = max(min(a, b), min(max(a, b), c));
         }
@@ -268,7 +388,7 @@ struct Hist {
             __syncthreads();
             for (int q = 0; q < 4 && j + q < kh * Z; ++q) {
                 uint32_t d[ND];
-                read_row(d, kStage + q * kRow + g4);
+                read_row(d, kStage + q * kStaged + g4);
                 nge = count_ge(d, nm, w, nge);
             }
             __syncthreads();
@@ -278,12 +398,19 @@ struct Hist {
         uint32_t am = (m << 8) + g4 + kPad;
         __syncthreads();
         unsigned char* out = dst + (long long)y0 * pitch;
-        auto step = [&](int y, int par) {
-            find(am, e, w);
+        int more = -32;      // the first walk starts from a guess and says nothing of the next
+        uint32_t ask = 0;
+        int asked = 0;
+        auto step = [&](auto coarse, int y, int par) {
+            if constexpr (decltype(coarse)::value) find_coarse(am, e, w, g4, (all - 1) / 2, more);
+            else find(am, e, w, more);
+            if (kCoarse && !decltype(coarse)::value && par == 1)
+                if (more >= 4 * kFar) *(lds_u32*)(uintptr_t)kAsk = 1;
             __syncthreads();
             // the counters change from here to the next barrier; the median
             // found and its rank in the next window do not depend on them
             asm volatile("" : "+v"(am), "+v"(e));
+            if (kCoarse && !decltype(coarse)::value && par == 1) ask = *(const lds_u32*)(uintptr_t)kAsk;
             m = ((am - kPad) >> 8) & 255u;
             if (inside && y < y1) out[vo] = (unsigned char)m;
             out += pitch;
@@ -292,19 +419,35 @@ struct Hist {
 #pragma unroll
             for (int q = 0; q < Z; ++q) {
                 uint32_t din[ND], dout[ND];
-                read_row(din, kStage + (uint32_t)((2 * par) * Z + q) * kRow + g4);
-                read_row(dout, kStage + (uint32_t)((2 * par + 1) * Z + q) * kRow + g4);
+                read_row(din, kStage + (uint32_t)((2 * par) * Z + q) * kStaged + g4);
+                read_row(dout, kStage + (uint32_t)((2 * par + 1) * Z + q) * kStaged + g4);
                 e = (int)count_ge(din, nm, w, (uint32_t)e);
                 gone = count_ge(dout, nm, w, gone);
             }
             e -= (int)gone;
             asm volatile("" : "+v"(e));
+            if (kCoarse && !decltype(coarse)::value && par == 1) {
+                asked = __builtin_amdgcn_readfirstlane((int)ask);
+                asm volatile("" : "+s"(asked));
+            }
             __syncthreads();
         };
-        for (int y = y0; y < y1; y += 2) {
-            step(y, 0);
-            step(y + 1, 1);
-        }
+        rows(
+            y0, y1, wave, lane,
+            [&](int y) {
+                step(std::false_type{}, y, 0);
+                step(std::false_type{}, y + 1, 1);
+                more = max(more - 2 * kFar, 0);
+                return asked != 0;
+            },
+            [&](int y) {
+                step(std::true_type{}, y, 0);
+                step(std::true_type{}, y + 1, 1);
+            },
+            [&](int n) {
+                if (lane == 0) *(lds_u32*)(uintptr_t)(kKeep + 4 * wave) = more >= kFar * n / 2 ? 1u : 0u;
+                more = 0;
+            });
     }
 
     template <class Row>
@@ -333,15 +476,14 @@ struct Hist {
                 for (int q = 0; q < P; ++q)
 #pragma unroll
                     for (int i = 0; i < NL; ++i)
-                        if (lane + 64 * i < kRow)
-                            *(lds_u8*)(uintptr_t)(kStage + (wave * P + q) * kRow + lane + 64 * i) = (uint8_t)b[q][i];
+                        *(lds_u8*)(uintptr_t)(kStage + (wave * P + q) * kStaged + lane + 64 * i) = (uint8_t)b[q][i];
                 fetch(j + 4);
                 __syncthreads();
                 const int q = wave * P + sub;
                 if (j + q < kh * Z) {
                     uint32_t d[1][ND];
-                    read_row(d[0], kStage + q * kRow + g4);
-                    update<0, NG, false>(d, g4, 1);
+                    read_row(d[0], kStage + q * kStaged + g4);
+                    update<0, NG, false, false>(d, g4, 1);
                 }
                 __syncthreads();
             }
@@ -369,30 +511,41 @@ struct Hist {
             for (int q = 0; q < Z; ++q)
 #pragma unroll
                 for (int i = 0; i < NF; ++i)
-                    if (fx + lane + 64 * i < kRow)
-                        *(lds_u8*)(uintptr_t)(kStage + ((2 * par + frow) * Z + q) * kRow + fx + lane + 64 * i) =
-                            (uint8_t)b[q][i];
+                    *(lds_u8*)(uintptr_t)(kStage + ((2 * par + frow) * Z + q) * kStaged + fx + lane + 64 * i) =
+                        (uint8_t)b[q][i];
         };
         fetch(buf[0], y0);
         put(buf[0], 0);
         fetch(buf[1], y0 + 1);
         fetch(buf[0], y0 + 2);
         __syncthreads();
-        auto step = [&](int y, int par, uint32_t (&b)[Z][NF]) {
+        uint32_t ask = 0;
+        auto step = [&](auto coarse, int y, int par, uint32_t (&b)[Z][NF]) {
             uint32_t d[Z][ND];
 #pragma unroll
-            for (int q = 0; q < Z; ++q) read_row(d[q], kStage + (uint32_t)((2 * par + leaves) * Z + q) * kRow + g4);
+            for (int q = 0; q < Z; ++q) read_row(d[q], kStage + (uint32_t)((2 * par + leaves) * Z + q) * kStaged + g4);
             put(b, par ^ 1);
             fetch(b, y + 3);
             const int one = leaves ? -1 : 1;
-            if (half) update<CH, NG, true>(d, g4, one);
-            else update<0, CH, true>(d, g4, one);
+            if (half) update<CH, NG, true, decltype(coarse)::value>(d, g4, one);
+            else update<0, CH, true, decltype(coarse)::value>(d, g4, one);
+            if (kCoarse && !decltype(coarse)::value && par == 1) ask = *(const lds_u32*)(uintptr_t)kAsk;
             __syncthreads();
         };
-        for (int y = y0; y < y1; y += 2) {
-            step(y, 0, buf[1]);
-            step(y + 1, 1, buf[0]);
-        }
+        rows(
+            y0, y1, kWaves + wave, lane,
+            [&](int y) {
+                step(std::false_type{}, y, 0, buf[1]);
+                step(std::false_type{}, y + 1, 1, buf[0]);
+                if constexpr (!kCoarse) return false;
+                asm volatile("" : "+v"(ask));      // looked at after the barrier
+                return __builtin_amdgcn_readfirstlane((int)ask) != 0;
+            },
+            [&](int y) {
+                step(std::true_type{}, y, 0, buf[1]);
+                step(std::true_type{}, y + 1, 1, buf[0]);
+            },
+            [](int) {});
     }
 };
 
@@ -426,6 +579,11 @@ template <int KW, int P>
 __global__ void __launch_bounds__(2 * 64 * kT / P)
 mf_hist_kernel_batched(const MfJob* __restrict__ jobs, int njobs, int nblocks)
 {
+    // not known to the compiler: it unrolls the first window's loops otherwise,
+    // and keeps more addresses from block to block than two work-groups on a CU
+    // have registers for
+    int kh = KW;
+    asm("" : "+s"(kh));
     for (int b = blockIdx.x; b < nblocks; b += gridDim.x) {
         int lo = 0, hi = njobs - 1;
         while (lo < hi) {
@@ -437,7 +595,7 @@ mf_hist_kernel_batched(const MfJob* __restrict__ jobs, int njobs, int nblocks)
         const int lb = b - j.block_begin;
         const int y0 = lb / j.nbx * kBatchRows;
         Hist<KW, P>::strip(j.src, j.dst, j.H, j.W, j.pitch, lb % j.nbx * Hist<KW, P>::kCols, y0,
-                           min(y0 + kBatchRows, j.H), KW);
+                           min(y0 + kBatchRows, j.H), kh);
         __syncthreads();   // the next block reuses the LDS
     }
 }

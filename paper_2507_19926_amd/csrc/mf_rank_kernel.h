@@ -262,7 +262,8 @@ struct Rank {
             const bool inside = x0 + ox < W;
             unsigned char* out = dst + (long long)y0 * pitch + (long long)(x0 + ox) * (int)sizeof(V);
             for (int y = 0; y < rows; ++y) {
-                int back = Hs::find(am, e, w);
+                int more = 0;
+                int back = Hs::find(am, e, w, more);
                 __syncthreads();
                 asm volatile("" : "+v"(am), "+v"(e), "+v"(back));
                 m = ((am - kPad) >> 8) & 255u;
@@ -283,7 +284,7 @@ struct Rank {
             for (int q = (wave - 2) * 2 + sub; q < kh; q += 12) {
                 uint32_t d[1][Hs::ND];
                 Hs::read_row(d[0], kIds + q * FS + g4);
-                Hs::template update<0, Hs::NG, false>(d, g4, 1);
+                Hs::template update<0, Hs::NG, false, false>(d, g4, 1);
             }
             __syncthreads();
             if (wave < 4) {
@@ -292,8 +293,8 @@ struct Rank {
                     uint32_t d[1][Hs::ND];
                     // past the last step the counters are not read any more
                     Hs::read_row(d[0], kIds + (uint32_t)(sub || y + 1 == rows ? y : y + kh) * FS + g4);
-                    if (wave == 3) Hs::template update<Hs::CH, Hs::NG, true>(d, g4, one);
-                    else Hs::template update<0, Hs::CH, true>(d, g4, one);
+                    if (wave == 3) Hs::template update<Hs::CH, Hs::NG, true, false>(d, g4, one);
+                    else Hs::template update<0, Hs::CH, true, false>(d, g4, one);
                     __syncthreads();
                 }
             } else {
