@@ -122,7 +122,7 @@ __device__ __forceinline__ uint32_t vmed3(uint32_t a, uint32_t b, uint32_t c)
 template <int ES, int CB>
 __global__ void __launch_bounds__(64 * kStripWaves)
 mf_strip3_kernel(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst, int H, int W,
-                 long long pitch, long long plane_stride, int dtype, int nbx, int aligned)
+                 long long pitch, long long plane_stride, int dtype, int nbx, int aligned, int by0)
 {
     src += (long long)blockIdx.y * plane_stride;   // plane = blockIdx.y
     dst += (long long)blockIdx.y * plane_stride;
@@ -131,7 +131,7 @@ mf_strip3_kernel(const unsigned char* __restrict__ src, unsigned char* __restric
     constexpr int NR = R + 2;                // input rows of a wave
     constexpr int D = kStripDepth;           // input rows in flight ahead of use
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int bx = blockIdx.x % nbx, by = blockIdx.x / nbx;
+    const int bx = blockIdx.x % nbx, by = by0 + (int)(blockIdx.x / nbx);
     const int x0 = bx * 64 * P + lane * P;    // first pixel of this lane's chunk
     const int y0 = (by * kStripWaves + wv) * R;
     if (y0 >= H) return;                      // whole wave; the kernel has no barriers
@@ -257,13 +257,19 @@ hipError_t strip3_launch(const void* src, void* dst, int planes, long long plane
     // whole-chunk loads and stores need 16-byte aligned rows
     const int aligned = ((uintptr_t)src % 16 == 0 && (uintptr_t)dst % 16 == 0 && pitch % 16 == 0 &&
                          plane_stride % 16 == 0) ? 1 : 0;
+    // a grid row of 2^32 threads or more wraps, without an error, so very tall
+    // images (from 2^28 rows on) take several launches
+    const int most = ((1 << 24) - 1) / nbx;          // block rows of a launch
     for (int p0 = 0; p0 < planes; p0 += 65535) {     // grid rows are planes
         const int np = planes - p0 < 65535 ? planes - p0 : 65535;
-        hipLaunchKernelGGL((mf_strip3_kernel<ES, CB>), dim3((unsigned)nbx * nby, np), dim3(64 * kStripWaves), 0, st,
-                           (const unsigned char*)src + p0 * plane_stride, (unsigned char*)dst + p0 * plane_stride,
-                           H, W, pitch, plane_stride, dtype, nbx, aligned);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        for (int by0 = 0; by0 < nby; by0 += most) {
+            const int nb = nby - by0 < most ? nby - by0 : most;
+            hipLaunchKernelGGL((mf_strip3_kernel<ES, CB>), dim3((unsigned)(nbx * nb), np), dim3(64 * kStripWaves), 0, st,
+                               (const unsigned char*)src + p0 * plane_stride, (unsigned char*)dst + p0 * plane_stride,
+                               H, W, pitch, plane_stride, dtype, nbx, aligned, by0);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }
