@@ -206,15 +206,32 @@ hipError_t allow_lds(F fn, size_t lds)
                             : hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
+// launch(p0, np) for planes [p0, p0 + np) at a time: a grid of 2^32 threads or
+// more wraps, without an error.
+template <class Launch>
+hipError_t by_planes(int64_t planes, int64_t plane_blocks, int threads, const Launch& launch)
+{
+    const int64_t most = ((1LL << 32) - 1) / threads / plane_blocks;
+    if (most < 1) return hipErrorInvalidValue;
+    for (int64_t p0 = 0; p0 < planes; p0 += most) {
+        launch(p0, planes - p0 < most ? planes - p0 : most);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <int K>
-hipError_t argmedian(const float* src, const float* med, int32_t* idx, unsigned blocks, size_t lds, int H, int W, int k,
+hipError_t argmedian(const float* src, const float* med, int32_t* idx, int64_t planes, size_t lds, int H, int W, int k,
                      int nbx, int nby, hipStream_t stream)
 {
     hipError_t e = allow_lds(mf_argmedian_kernel<K>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mf_argmedian_kernel<K>, dim3(blocks), dim3(kThreads), lds, stream, (const uint32_t*)src,
-                       (const uint32_t*)med, idx, H, W, k, nbx, nby);
-    return hipGetLastError();
+    return by_planes(planes, (int64_t)nbx * nby, kThreads, [&](int64_t p0, int64_t np) {
+        const int64_t o = p0 * H * W;
+        hipLaunchKernelGGL(mf_argmedian_kernel<K>, dim3((unsigned)(np * nbx * nby)), dim3(kThreads), lds, stream,
+                           (const uint32_t*)src + o, (const uint32_t*)med + o, idx + o, H, W, k, nbx, nby);
+    });
 }
 
 template <int RB, int ROWS, int THREADS>
@@ -222,17 +239,17 @@ hipError_t grad_bits(const float* gout, const int32_t* idx, float* gin, int64_t 
                      hipStream_t stream)
 {
     const int nbx = (W + kBX - 1) / kBX, nby = (H + ROWS - 1) / ROWS;
-    const long long blocks = planes * (long long)nbx * nby;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int lw = kBX + k - 1, lh = ROWS + k - 1;
     const size_t lds = (size_t)((k * RB + 31) / 32 * kBX * ROWS + lw * lh) * 4;
     const uint32_t inv_w = W == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (unsigned)W);
     const uint32_t inv_lw = ((1u << 20) + lw - 1) / lw;
     hipError_t e = allow_lds(mf_grad_bits_kernel<RB, ROWS, THREADS>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((mf_grad_bits_kernel<RB, ROWS, THREADS>), dim3((unsigned)blocks), dim3(THREADS), lds, stream, gout,
-                       idx, gin, H, W, k, nbx, nby, inv_w, inv_lw);
-    return hipGetLastError();
+    return by_planes(planes, (int64_t)nbx * nby, THREADS, [&](int64_t p0, int64_t np) {
+        const int64_t o = p0 * H * W;
+        hipLaunchKernelGGL((mf_grad_bits_kernel<RB, ROWS, THREADS>), dim3((unsigned)(np * nbx * nby)), dim3(THREADS), lds,
+                           stream, gout + o, idx + o, gin + o, H, W, k, nbx, nby, inv_w, inv_lw);
+    });
 }
 
 }  // namespace
@@ -241,14 +258,12 @@ hipError_t mf_ag_argmedian_launch(const float* src, const float* med, int32_t* i
                                   int W, int k, hipStream_t stream)
 {
     const int nbx = (W + kBX - 1) / kBX, nby = (H + kAY - 1) / kAY;
-    const long long blocks = planes * (long long)nbx * nby;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t lds = (size_t)(kBX + k - 1) * (kAY + k - 1) * 4;
     switch (k) {
-#define MF_CASE(K) case K: return argmedian<K>(src, med, idx, (unsigned)blocks, lds, H, W, k, nbx, nby, stream);
+#define MF_CASE(K) case K: return argmedian<K>(src, med, idx, planes, lds, H, W, k, nbx, nby, stream);
     MF_CASE(3) MF_CASE(5) MF_CASE(7) MF_CASE(9) MF_CASE(11) MF_CASE(13) MF_CASE(15)
 #undef MF_CASE
-    default: return argmedian<0>(src, med, idx, (unsigned)blocks, lds, H, W, k, nbx, nby, stream);
+    default: return argmedian<0>(src, med, idx, planes, lds, H, W, k, nbx, nby, stream);
     }
 }
 
@@ -260,15 +275,15 @@ hipError_t mf_ag_grad_launch(const float* gout, const int32_t* idx, float* gin, 
     if (k <= 15) return grad_bits<16, 16, 512>(gout, idx, gin, planes, H, W, k, stream);
     if (k <= 31) return grad_bits<32, 8, 512>(gout, idx, gin, planes, H, W, k, stream);
     const int nby = (H + kBY - 1) / kBY;
-    const long long blocks = planes * (long long)nbx * nby;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t lds = (size_t)(kBX + k - 1) * (kBY + k - 1) * 8;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)mf_grad_gather_kernel,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(mf_grad_gather_kernel, dim3((unsigned)blocks), dim3(kThreads), lds, stream, gout,
-                       idx, gin, H, W, k, nbx, nby);
-    return hipGetLastError();
+    return by_planes(planes, (int64_t)nbx * nby, kThreads, [&](int64_t p0, int64_t np) {
+        const int64_t o = p0 * H * W;
+        hipLaunchKernelGGL(mf_grad_gather_kernel, dim3((unsigned)(np * nbx * nby)), dim3(kThreads), lds, stream, gout + o,
+                           idx + o, gin + o, H, W, k, nbx, nby);
+    });
 }

@@ -3,7 +3,7 @@ them was refused by the kernels that ran them before."""
 import torch
 import pytest
 
-from paper_2507_19926_amd.ops import median_filter
+from paper_2507_19926_amd.ops import median_filter, median_filter_argmedian, median_filter_backward
 
 pytestmark = pytest.mark.gpu
 
@@ -18,3 +18,19 @@ def test_strips_of_a_very_tall_image():
     a, b, c = torch.cat([x[:1], x[:-1]]), x, torch.cat([x[1:], x[-1:]])
     want = torch.maximum(torch.minimum(a, b), torch.minimum(torch.maximum(a, b), c))
     assert torch.equal(y, want)
+
+
+@pytest.mark.parametrize("k", [3, 9, 31, 33])
+def test_gradient_of_many_tiny_planes(k):
+    """More than 2^24 planes, a work-group each, against calls of a few of
+    them from either end and from the middle."""
+    n = (1 << 24) + 7
+    g = torch.Generator(device="cuda").manual_seed(k)
+    x = torch.rand((n, 2, 3), generator=g, device="cuda")
+    up = torch.rand((n, 2, 3), generator=g, device="cuda")
+    y, idx = median_filter_argmedian(x, k)
+    gi = median_filter_backward(up, idx, k)
+    for a, b in ((0, 999), ((1 << 23) - 500, (1 << 23) + 500), (n - 999, n)):
+        ys, ids = median_filter_argmedian(x[a:b].contiguous(), k)
+        assert torch.equal(y[a:b], ys) and torch.equal(idx[a:b], ids)
+        assert torch.equal(gi[a:b], median_filter_backward(up[a:b].contiguous(), ids, k))
