@@ -136,14 +136,23 @@ hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plan
     e = allow_lds(fn, tall ? kTallSlots + kw / 2 : slot_of(dtype, kw, kh, false), dev);
     if (e != hipSuccess) return e;
     const int ns = (H + R - 1) / R;
-    if ((long long)ncol * ns > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const long long blocks = (long long)ncol * ns;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    // a grid has fewer than 2^32 threads a row: 2^23 - 1 regions of the ranked
+    // kernels, the others' strips never come to so many
+    const long long most = rank ? ((1LL << 32) - 1) / k.threads : blocks;
     for (int p0 = 0; p0 < planes; p0 += 65535) {     // grid rows are planes
         const int np = planes - p0 < 65535 ? planes - p0 : 65535;
         const unsigned char* s8 = (const unsigned char*)src + p0 * plane_stride;
         unsigned char* d8 = (unsigned char*)dst + p0 * plane_stride;
-        void* args[] = {&s8, &d8, &H, &W, &pitch, &plane_stride, (void*)&ncol, (void*)&R, &kh, &is_float};   // is_float: ranked kernels
-        e = hipLaunchKernel(fn, dim3((unsigned)(ncol * ns), np), dim3(k.threads), args, lds, stream);
-        if (e != hipSuccess) return e;
+        for (long long from = 0; from < blocks; from += most) {
+            int b0 = (int)from;
+            const long long nb = blocks - from < most ? blocks - from : most;
+            void* args[] = {&s8,         &d8,       &H,  &W,        &pitch, &plane_stride,
+                            (void*)&ncol, (void*)&R, &kh, &is_float, &b0};     // the last two: ranked kernels
+            e = hipLaunchKernel(fn, dim3((unsigned)nb, np), dim3(k.threads), args, lds, stream);
+            if (e != hipSuccess) return e;
+        }
     }
     return hipSuccess;
 }

@@ -411,10 +411,10 @@ struct Rank {
 template <int KW, int KHM, class V, bool TALL>
 __global__ void __launch_bounds__(kRankThreads)
 mf_rank_kernel(const unsigned char* __restrict__ src, unsigned char* dst, int H, int W, long long pitch,
-               long long plane_stride, int ncol, int R, int kh, int is_float)
+               long long plane_stride, int ncol, int R, int kh, int is_float, int b0)
 {
     typedef Rank<KW, KHM, V, TALL> Rk;
-    const int cb = (int)blockIdx.x % ncol, s = (int)blockIdx.x / ncol;
+    const int b = b0 + (int)blockIdx.x, cb = b % ncol, s = b / ncol;
     const long long po = (long long)blockIdx.y * plane_stride;   // plane = blockIdx.y
     Rk::region(src + po, dst + po, H, W, pitch, cb * Rk::kCols, s * R, min((s + 1) * R, H), kh, is_float != 0);
 }

@@ -3,6 +3,7 @@ them was refused by the kernels that ran them before."""
 import torch
 import pytest
 
+from paper_2507_19926_amd import _lib
 from paper_2507_19926_amd.ops import median_filter, median_filter_argmedian, median_filter_backward
 
 pytestmark = pytest.mark.gpu
@@ -34,3 +35,11 @@ def test_gradient_of_many_tiny_planes(k):
         ys, ids = median_filter_argmedian(x[a:b].contiguous(), k)
         assert torch.equal(y[a:b], ys) and torch.equal(idx[a:b], ids)
         assert torch.equal(gi[a:b], median_filter_backward(up[a:b].contiguous(), ids, k))
+
+
+def test_regions_of_a_very_wide_image():
+    """2^30 columns: a region more than a launch of the ranked kernels takes."""
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.rand((1, 1 << 30), generator=g, device="cuda")
+    y = median_filter(x, 21, variant=_lib.MF_VARIANT_DATA_AWARE, form=3)
+    assert torch.equal(y, median_filter(x, 21, variant=_lib.MF_VARIANT_OBLIVIOUS))
