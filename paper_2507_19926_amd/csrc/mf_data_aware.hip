@@ -761,6 +761,26 @@ const DaEntry* da_find(int dtype, int k, int tw, int th, int group, int kh = 0, 
 std::mutex g_da_mu;
 const uint32_t* g_da_blob_dev[64];
 
+// Copies the schedules to the current device. The first call that needs them
+// may be one that is being captured: the copy takes a stream of its own, which
+// nothing captures, and the thread lets that pass for its time.
+hipError_t da_blob_copy(void* dst)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) return e;
+    hipStream_t s = nullptr;
+    e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e == hipSuccess) {
+        e = hipMemcpyAsync(dst, mf_da_blob_host, sizeof(uint32_t) * MF_DA_BLOB_WORDS, hipMemcpyHostToDevice, s);
+        const hipError_t f = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = f;
+        (void)hipStreamDestroy(s);
+    }
+    const hipError_t f = hipThreadExchangeStreamCaptureMode(&mode);
+    return e == hipSuccess ? f : e;
+}
+
 // Device copy of the schedules for the current device (copied once).
 hipError_t da_blob(const uint32_t** out)
 {
@@ -770,11 +790,9 @@ hipError_t da_blob(const uint32_t** out)
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     std::lock_guard<std::mutex> lock(g_da_mu);
     if (!g_da_blob_dev[dev]) {
-        e = hipMemcpyToSymbol(HIP_SYMBOL(mf_da_blob), mf_da_blob_host, sizeof(uint32_t) * MF_DA_BLOB_WORDS, 0,
-                              hipMemcpyHostToDevice);
-        if (e != hipSuccess) return e;
         void* p = nullptr;
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(mf_da_blob));
+        if (e == hipSuccess) e = da_blob_copy(p);
         if (e != hipSuccess) return e;
         for (int dt = MF_U8; dt <= MF_U32; ++dt)
             for (int bt = 0; bt < 3; ++bt) {
