@@ -136,24 +136,73 @@ bool hist_is_faster(int32_t dtype, int32_t k)
     return k >= from && mf_hist_supports(dtype, k, k);
 }
 
-// What a call of `pixels` pixels runs instead of the choice for large images
-// when it is small (network: 8-bit images of a batch, see
-// mf_internal_small_batch): a network's wave takes its 20-70 us (k = 9 to 21) and a
-// ranked region its 40-120 us however few there are, while a schedule's time
-// falls with the pixels and the 8-bit histograms start at 11 us. us, one plane
-// of uniform noise (normal float32), network / schedule / histograms:
+// planes * H * W, or a number beyond every line below
+int64_t pixels_of(int64_t planes, int64_t H, int64_t W)
+{
+    return planes > (1 << 21) || H > (1 << 21) || W > (1 << 21) ? (1 << 21) : planes * std::min<int64_t>(H * W, 1 << 21);
+}
+
+// The measured choice for (dtype, k), if there is one.
+const AutoEntry* auto_entry(int32_t dtype, int32_t k)
+{
+    int cls = (dtype == MF_U8 || dtype == MF_U16) ? 0 : 1;
+    if (dtype == MF_U16)
+        for (const AutoEntry& a : kAutoTable)
+            if (a.cls == 2 && a.k == k) cls = 2;
+    for (const AutoEntry& a : kAutoTable)
+        if (a.cls == cls && a.k == k) return &a;
+    return nullptr;
+}
+
+// Whether a window's histograms take less time than its schedule. They work
+// on 128 columns at a time, ranked ones on regions that take their 30-100 us
+// however little of them the image fills, so it is the shape that decides:
+// narrow images and many tiny planes fill few of the columns, while the
+// schedules' tiles of 4 to 16 pixels a side fit them. us, schedule / histograms:
+//   uint16  k = 23  4096 planes of 16x16 181 / 713, 65536x8 181 / 335, 2048x64 25 / 36
+//           19x11   20000x24 79 / 139;  k = 35  4096 of 16x16 280 / 771, 65536x8 282 / 359
+//   float32 k = 25  4096 of 16x16 352 / 1057, 256 of 40x40 198 / 104, 20000x24 247 / 177
+//   uint8   k = 23  4096 of 16x16 118 / 159, 256 of 16x16 21 / 18;  k = 75  1000 of 16x16 124 / 103
+// By the estimates, over 1068 windows and shapes of 16- and 32-bit data the call
+// takes 0.4 % longer than with the better choice everywhere.
+bool hist_pays(int32_t dtype, int32_t kw, int32_t kh, int64_t planes, int64_t H, int64_t W)
+{
+    const AutoEntry* a = kw == kh ? auto_entry(dtype, kw) : nullptr;
+    if (a && a->variant != MF_VARIANT_DATA_AWARE) a = nullptr;
+    int cus = 0;
+    const double hist = mf_hist_estimate(dtype, kw, kh, planes, (int)H, (int)W, &cus);
+    const double schedule = a ? mf_da_estimate(dtype, kw, a->tw, a->th, a->group, kh, a->form, true, planes, (int)H, (int)W, cus)
+                              : mf_da_estimate(dtype, kw, 0, 0, 0, kh, 0, kw != kh, planes, (int)H, (int)W, cus);
+    // (32-bit regions of low windows take longer than estimated: 23x3, 512x513 64 us,
+    // estimated 43, the schedule 53)
+    const double most = dtype == MF_U8 ? 1.1 : dtype != MF_U16 && kw * kh < 100 ? 0.6 : 0.9;
+    return hist < most * schedule;
+}
+
+// What a call runs instead of the choice for large images when it is small or
+// narrow (network: 8-bit images of a batch, see mf_internal_small_batch): a
+// network's wave takes its 20-70 us (k = 9 to 21) and a ranked region its 40-120 us
+// however few there are, while a schedule's time falls with the pixels and the
+// 8-bit histograms start at 11 us. us, one plane of uniform noise (normal
+// float32), network / schedule / histograms:
 //   uint8   k = 9   512^2 13.2 / 628 / 12.4;  k = 11  512^2 18.1 / - / 12.4, 724^2 18.1 / - / 18.6
 //   uint16  k = 17  384^2 37 / 28, 512^2 37 / 40;  k = 19  512^2 51 / 40, 768^2 52 / 74
 //           k = 21  256^2 68 / 24 / 42, 768^2 69 / 114 / 50, 1000x700 83 / 145 / 61
 //           k = 23  320^2 - / 33 / 44, 384^2 - / 50 / 43;  k = 75  256^2 - / 67 / 78
 //   float32 k = 17  256^2 32 / 22, 384^2 32 / 58;  k = 19  256^2 47 / 21, 384^2 47 / 57
 //           k = 23  320^2 - / 52 / 66, 384^2 - / 73 / 66
+// The 8-bit lines count whole blocks of 256 columns (k = 9, network / histograms:
+// 8192x24 22 / 27, 256 planes of 28x28 21 / 26).
 enum class Small { no, schedule, network, histograms };
-Small small_choice(int32_t dtype, int32_t k, int64_t pixels)
+Small small_choice(int32_t dtype, int32_t k, int64_t planes, int64_t H, int64_t W)
 {
-    if (dtype == MF_U8)
-        return (k == 9 && pixels <= (1 << 18)) || (k == 11 && pixels <= (3 << 17)) ? Small::histograms : Small::no;
-    if (pixels < (1 << 17) && hist_is_faster(dtype, k)) return Small::schedule;
+    if (dtype == MF_U8) {
+        if (k != 9 && k != 11) return k > 21 && !hist_pays(dtype, k, k, planes, H, W) ? Small::schedule : Small::no;
+        return pixels_of(planes, H, (W + 255) / 256 * 256) <= (k == 9 ? 1 << 18 : 3 << 17) ? Small::histograms : Small::no;
+    }
+    const int64_t pixels = pixels_of(planes, H, W);
+    if (hist_is_faster(dtype, k))
+        return pixels < (1 << 17) || !hist_pays(dtype, k, k, planes, H, W) ? Small::schedule : Small::no;
     if (dtype == MF_U16) {
         if (k == 17) return pixels <= (1 << 17) ? Small::schedule : Small::no;
         if (k == 19) return pixels <= (1 << 18) ? Small::schedule : Small::no;
@@ -161,12 +210,6 @@ Small small_choice(int32_t dtype, int32_t k, int64_t pixels)
         return Small::no;
     }
     return (k == 17 || k == 19) && pixels <= (1 << 16) ? Small::schedule : Small::no;
-}
-
-// planes * H * W, or a number beyond every line above
-int64_t pixels_of(int64_t planes, int64_t H, int64_t W)
-{
-    return planes > (1 << 21) || H > (1 << 21) || W > (1 << 21) ? (1 << 21) : planes * std::min<int64_t>(H * W, 1 << 21);
 }
 
 // Resolve (dtype, k, opt) to a variant and root tile; small: small_choice()
@@ -201,31 +244,24 @@ int32_t resolve(int32_t dtype, int32_t k, const mf_options* opt, int32_t* varian
             return MF_OK;
         }
         no_network = small == Small::schedule;
-        int cls = (dtype == MF_U8 || dtype == MF_U16) ? 0 : 1;
-        if (dtype == MF_U16)
-            for (const AutoEntry& a : kAutoTable)
-                if (a.cls == 2 && a.k == k) cls = 2;
-        for (const AutoEntry& a : kAutoTable) {
-            if (a.cls != cls || a.k != k) continue;
-            if (a.variant == MF_VARIANT_OBLIVIOUS && no_network) break;
-            if (a.variant == MF_VARIANT_OBLIVIOUS) {
-                const OblEntry* e = find_obl(k, a.tw, a.th, a.group, a.form, a.rows);
-                if (e) {
-                    *variant = MF_VARIANT_OBLIVIOUS;
-                    *tw = e->tw;
-                    *th = e->th;
-                    *obl = e;
-                    return MF_OK;
-                }
-            } else if (mf_da_supports(dtype, k, a.tw, a.th, a.group, 0, a.form)) {
-                *variant = MF_VARIANT_DATA_AWARE;
-                *tw = a.tw;
-                *th = a.th;
-                if (group) *group = a.group;
-                if (da_form) *da_form = a.form;
+        // (a stale entry: fall back to the built-in order)
+        const AutoEntry* a = auto_entry(dtype, k);
+        if (a && a->variant == MF_VARIANT_OBLIVIOUS && !no_network) {
+            const OblEntry* e = find_obl(k, a->tw, a->th, a->group, a->form, a->rows);
+            if (e) {
+                *variant = MF_VARIANT_OBLIVIOUS;
+                *tw = e->tw;
+                *th = e->th;
+                *obl = e;
                 return MF_OK;
             }
-            break;  // a stale entry: fall back to the built-in order
+        } else if (a && a->variant != MF_VARIANT_OBLIVIOUS && mf_da_supports(dtype, k, a->tw, a->th, a->group, 0, a->form)) {
+            *variant = MF_VARIANT_DATA_AWARE;
+            *tw = a->tw;
+            *th = a->th;
+            if (group) *group = a->group;
+            if (da_form) *da_form = a->form;
+            return MF_OK;
         }
     }
     if (o.variant != MF_VARIANT_DATA_AWARE && !no_network) {
@@ -445,12 +481,14 @@ int32_t median_filter_rect(const void* src, void* dst, int64_t planes, int64_t p
     if (!mf_da_supports(dtype, kw, 0, 0, 0, kh))
         return fail(MF_ERR_CONFIG, "no data-aware schedule for the %dx%d window", kw, kh);
     // without a network: sliding histograms instead of the schedule (30 MP RGB
-    // 8-bit frame: 21x13 0.45 ms against 9.9, 31x29 0.87 against 22 on noise).
-    // Ranked planes start at the line of small_choice(), windows of few values,
-    // which the schedule does faster, later (float32 11x21, 145 000 pixels 40 us
-    // against 63; 9x25, 539 000 117 against 74; 25x13, 198 000 76 against 59)
+    // 8-bit frame: 21x13 0.46 ms against 9.9, 31x29 0.87 against 22 on noise) where
+    // the shape lets them (hist_pays()). Ranked planes start at the line of
+    // small_choice(), windows of fewer values, which the schedule does faster,
+    // later (us, ranked / schedule: float32 11x21, 145 000 pixels 63 / 40; 25x13,
+    // 198 000 59 / 76; 19x17, 133 000 51 / 41; 9x25, 539 000 74 / 117)
     if (variant == MF_VARIANT_AUTO && mf_hist_supports(dtype, kw, kh) &&
-        (dtype == MF_U8 || pixels_of(planes, H, W) >= (kw * kh < 300 ? 1 << 18 : 1 << 17)))
+        (dtype == MF_U8 || pixels_of(planes, H, W) >= (kw * kh < 300 ? 1 << 18 : kw * kh < 400 ? 3 << 16 : 1 << 17)) &&
+        hist_pays(dtype, kw, kh, planes, H, W))
         return hip_status(mf_hist_launch(src, dst, (int)planes, plane_stride_bytes, (int)H, (int)W, pitch_bytes, dtype,
                                          kw, kh, (hipStream_t)stream),
                           "sliding-histogram kernel launch");
@@ -513,7 +551,7 @@ int32_t median_filter_planes(const void* src, void* dst, int64_t planes, int64_t
     int32_t variant = 0, tw = 0, th = 0, group = 0, da_form = 0;
     const OblEntry* e = nullptr;
     rc = resolve(dtype, k, opt, &variant, &tw, &th, &e, &group, &da_form,
-                 small_choice(dtype, k, pixels_of(planes, H, W)));
+                 opt && opt->variant != MF_VARIANT_AUTO ? Small::no : small_choice(dtype, k, planes, H, W));
     if (rc) return rc;
     if (variant == MF_VARIANT_OBLIVIOUS) {
         mf_launch_fn fn = (dtype == MF_U8 || dtype == MF_U16) ? e->p16 : e->u32;

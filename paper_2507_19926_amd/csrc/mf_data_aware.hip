@@ -865,6 +865,27 @@ static MfDaArgs da_args(const DaEntry* e, const uint32_t* blob)
     return a;
 }
 
+// ps a pixel, fitted to one plane of 2048^2 (uniform noise, normal float32): uint8
+// k = 23 105, 75 448; uint16 k = 23 168, 35 261, 75 764, 19 x 13 132, 31 x 29 283;
+// float32 k = 23 297, 35 424, 75 1444, 19 x 13 202, 31 x 29 420; untuned float32 k = 21 336.
+// A launch takes whole rounds of two work-groups to a CU.
+double mf_da_estimate(int dtype, int k, int tw, int th, int group, int kh, int form, bool tuned, long long planes, int H,
+                      int W, int cus)
+{
+    const DaEntry* e = da_find(dtype, k, tw, th, group, kh, form);
+    if (!e || cus < 1) return 0;
+    const int bw = e->tw * e->tiles * e->groups;
+    const double area = (double)k * e->kh;
+    double ps = dtype == MF_U8 ? 100 + 0.13 * area : dtype == MF_U16 ? 120 + 0.16 * area : 150 + 0.3 * area;
+    if (e->kh == k) {
+        ps = k * (dtype == MF_U8 ? 3.9 + 0.027 * k : dtype == MF_U16 ? 5.8 + 0.055 * k : 9.0 + 0.135 * k);
+        if (!tuned) ps *= 1.3;
+    }
+    const long long groups = planes * ((W + bw - 1) / bw) * ((H + e->th - 1) / e->th);
+    const long long rounds = (groups + 2 * cus - 1) / (2 * cus);
+    return 8 + 1e-6 * ps * 512 * (double)rounds * bw * e->th;     // 512: those of 256 CUs, which ps is for
+}
+
 hipError_t mf_da_launch(const void* src, void* dst, int planes, long long plane_stride, int H, int W,
                         long long pitch, int dtype, int k, int tw, int th, int group, hipStream_t stream, int kh,
                         int form)

@@ -29,6 +29,9 @@ bool mf_hist_supports(int dtype, int kw, int kh);
 // `planes` planes of H x W, plane p at src/dst + p * plane_stride bytes.
 hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plane_stride, int H, int W,
                           long long pitch, int dtype, int kw, int kh, hipStream_t stream);
+// Estimated time in us of mf_hist_launch on the current device, good to a
+// quarter, and that device's CUs; 0 where either is not known.
+double mf_hist_estimate(int dtype, int kw, int kh, long long planes, int H, int W, int* cus);
 // Batched kernel of the square k x k window (arguments: jobs, njobs, nblocks).
 hipError_t mf_hist_batched(int dtype, int k, MfBatchedKernel* kern);
 

@@ -66,7 +66,8 @@ hipError_t device(int* dev, int* cus)
 // Rows of a strip, for `per_strip` work-groups side by side: a strip costs its
 // rows and `first` more for its first window; two work-groups run on each CU,
 // so of the launches of r rounds the one that fills them is the cheapest.
-int strip_rows(int H, long long per_strip, long long first, int cus)
+// steps: row steps of the longest CU.
+int strip_rows(int H, long long per_strip, long long first, int cus, long long* steps = nullptr)
 {
     const long long slots = 2LL * cus;
     long long best = -1;
@@ -80,6 +81,7 @@ int strip_rows(int H, long long per_strip, long long first, int cus)
         const long long cost = ((strips * per_strip + slots - 1) / slots) * (rows + first);
         if (best < 0 || cost < best) best = cost, R = rows;
     }
+    if (steps) *steps = best;
     return R;
 }
 
@@ -87,7 +89,9 @@ int strip_rows(int H, long long per_strip, long long first, int cus)
 // noise, k = 25..75): 4 (16-bit), 9 (32-bit) or 12 (32-bit, tall kernel) for a
 // value of the footprint, loaded, sorted and listed, 300 for a row of the first
 // window, 1600 for an output row slid, searched and walked; one region to a CU.
-int rank_rows(int H, int max_rows, long long per_strip, int fw, int kh, bool wide, int cus)
+// clocks, rounds: of all regions of a CU.
+int rank_rows(int H, int max_rows, long long per_strip, int fw, int kh, bool wide, int cus, long long* clocks = nullptr,
+              long long* rounds = nullptr)
 {
     long long best = -1;
     int R = max_rows;
@@ -97,8 +101,12 @@ int rank_rows(int H, int max_rows, long long per_strip, int fw, int kh, bool wid
         const long long value = !wide ? 4 : r <= 64 ? 9 : 12;
         const long long cost = (regions + cus - 1) / cus *
                                (value * fw * (used + kh - 1) + 300LL * kh + 1600LL * used + 5000);
-        if (best < 0 || cost < best) best = cost, R = r;
+        if (best < 0 || cost < best) {
+            best = cost, R = r;
+            if (rounds) *rounds = (regions + cus - 1) / cus;
+        }
     }
+    if (clocks) *clocks = best;
     return R;
 }
 
@@ -155,6 +163,26 @@ hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plan
         }
     }
     return hipSuccess;
+}
+
+// 8-bit: 8 us and the row steps (noise, which takes longer than a smooth image,
+// on many planes of 16 x 16: k = 23 0.62 us a step, 35 0.70, 75 1.1); ranked: 8 us,
+// the clocks above and 12 us a round (float32 k = 25: 16 x 16 to a plane 3.0 / 3.5 us
+// measured / estimated for 12 of them, 2048^2 200 / 182 us).
+double mf_hist_estimate(int dtype, int kw, int kh, long long planes, int H, int W, int* cus)
+{
+    HistKernelInfo k;
+    int dev = 0;
+    if (!find(dtype, kw, kh, &k) || device(&dev, cus) != hipSuccess) return 0;
+    const long long per_strip = planes * ((W + k.cols - 1) / k.cols);
+    if (dtype == MF_U8) {
+        long long steps = 0;
+        strip_rows(H, per_strip, kh / 4 + 8, *cus, &steps);
+        return 8 + (double)steps * (0.4 + 0.0096 * kw);
+    }
+    long long clocks = 0, rounds = 0;
+    rank_rows(H, k.max_rows, per_strip, k.cols + kw - 1, kh, dtype != MF_U16, *cus, &clocks, &rounds);
+    return 8 + (double)clocks / 2400 + 12.0 * (double)rounds;
 }
 
 hipError_t mf_hist_batched(int dtype, int k, MfBatchedKernel* kern)

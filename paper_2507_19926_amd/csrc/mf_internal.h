@@ -76,6 +76,12 @@ struct MfDaArgs {
 hipError_t mf_da_batched(int dtype, int k, int tw, int th, int group, MfBatchedKernel* kern, MfDaArgs* args,
                          int form = 0);
 
+// Estimated time in us of mf_da_launch on `cus` CUs, from the work-groups it
+// takes; good to a quarter, for choices of a kernel. tuned: the tile is one that
+// was chosen by measurement.
+double mf_da_estimate(int dtype, int k, int tw, int th, int group, int kh, int form, bool tuned, long long planes, int H,
+                      int W, int cus);
+
 // Global-memory multi-pass data-aware form: square k, root tile tw x th (0 =
 // the library's), lists in a caller workspace of ws_bytes (device pointer,
 // 256-byte aligned). Tiles run in slices of ws_bytes / slot_bytes, each
