@@ -832,8 +832,12 @@ int32_t median_filter_3d(const void* src, void* dst, int64_t D, int64_t H, int64
     // 0.52 against 4.61) unless they are too narrow for a work-group's 128
     // columns (128 x 128 x W, us: k = 3 W = 52 98 against 74, W = 70 98 against
     // 138; k = 5 W = 8 53 against 26, W = 32 58 against 76; k = 7 W = 8 64 against
-    // 38, W = 32 67 against 115)
-    if (mf_hist3_supports(dtype, k) && W > (k == 3 ? 64 : k == 5 ? 16 : 8))
+    // 38, W = 32 67 against 115) or have so few voxels that the histograms' first
+    // windows take longer than the whole schedule (k = 15: 128 x 4 x 48 85 against
+    // 42, 64 x 16 x 32 85 against 41, 16 x 64 x 128 85 against 123): by estimates
+    int cus = 0;
+    if (mf_hist3_supports(dtype, k) && W > (k == 3 ? 64 : k == 5 ? 16 : 8) &&
+        mf_hist3_estimate((int)D, (int)H, (int)W, k, &cus) < 1.1 * mf_da3_estimate(dtype, k, (int)D, (int)H, (int)W, cus))
         return hip_status(mf_hist3_launch(src, dst, (int)D, (int)H, (int)W, pitch_bytes, slice_bytes, k, st),
                           "3-D sliding-histogram kernel launch");
     return hip_status(mf_da3_launch(src, dst, (int)D, (int)H, (int)W, pitch_bytes, slice_bytes, dtype, k, st),

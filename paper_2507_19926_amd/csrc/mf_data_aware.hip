@@ -1066,6 +1066,17 @@ void mf_da3_tile(int dtype, int k, int* tw, int* th, int* tz)
     *tz = e ? e->tz : 0;
 }
 
+// ps a voxel of uint8 noise, 128 x 256 x 256: k = 3 62, 5 128, 7 198, 9 276, 15 814.
+double mf_da3_estimate(int dtype, int k, int D, int H, int W, int cus)
+{
+    const DaEntry* e = da3_find(dtype, k);
+    if (!e || cus < 1) return 0;
+    const int bw = e->tw * e->groups;
+    const long long groups = (long long)((W + bw - 1) / bw) * ((H + e->th - 1) / e->th) * ((D + e->tz - 1) / e->tz);
+    const long long rounds = (groups + 2 * cus - 1) / (2 * cus);
+    return 8 + 1e-6 * (15 + 5.0 * k + 3.3 * k * k) * 512 * (double)rounds * bw * e->th * e->tz;
+}
+
 hipError_t mf_da3_launch(const void* src, void* dst, int D, int H, int W, long long pitch, long long slice, int dtype,
                          int k, hipStream_t stream)
 {

@@ -38,5 +38,6 @@ hipError_t mf_hist_batched(int dtype, int k, MfBatchedKernel* kern);
 // 3-D boxes, cubic k x k x k, of a D x H x W volume (rows pitch bytes apart,
 // slices slice bytes).
 bool mf_hist3_supports(int dtype, int k);
+double mf_hist3_estimate(int D, int H, int W, int k, int* cus);     // us, as mf_hist_estimate
 hipError_t mf_hist3_launch(const void* src, void* dst, int D, int H, int W, long long pitch, long long slice, int k,
                            hipStream_t stream);

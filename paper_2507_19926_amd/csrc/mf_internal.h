@@ -98,6 +98,7 @@ hipError_t mf_dag_launch(const void* src, void* dst, int planes, long long plane
 // a D x H x W volume, rows pitch bytes apart, slices slice bytes apart.
 bool mf_da3_supports(int dtype, int k);
 int mf_da3_max_k();
+double mf_da3_estimate(int dtype, int k, int D, int H, int W, int cus);   // us, as mf_da_estimate; 8-bit data
 void mf_da3_tile(int dtype, int k, int* tw, int* th, int* tz);
 hipError_t mf_da3_launch(const void* src, void* dst, int D, int H, int W, long long pitch, long long slice, int dtype,
                          int k, hipStream_t stream);

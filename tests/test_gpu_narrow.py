@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2507_19926_amd import _lib
 from paper_2507_19926_amd import workloads as wl
-from paper_2507_19926_amd.ops import median_filter, median_filter_rect
+from paper_2507_19926_amd.ops import median_filter, median_filter_3d, median_filter_rect
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +49,12 @@ def test_rectangles(dtype, kw, kh, shape):
     got = median_filter_rect(x, kw, kh).cpu().numpy()
     _sampled(img, kw, kh, got)
     assert got.tobytes() == median_filter_rect(x, kw, kh, variant=_lib.MF_VARIANT_DATA_AWARE).cpu().numpy().tobytes()
+
+
+@pytest.mark.parametrize("k", [3, 5, 9, 15])
+@pytest.mark.parametrize("shape", [(64, 4, 48), (4, 8, 200), (20, 30, 70)])
+def test_boxes_of_few_voxels(k, shape):
+    D, H, W = shape
+    vol = wl.uniform_plane(D * H, W, np.uint8, seed=k).reshape(shape)
+    got = median_filter_3d(torch.from_numpy(vol).cuda(), k).cpu().numpy()
+    assert np.array_equal(got, oracle.median_filter_3d(vol, k))
