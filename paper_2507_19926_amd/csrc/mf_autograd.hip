@@ -19,15 +19,13 @@ namespace {
 
 constexpr int kBX = 64, kBY = 4;           // output block of one work-group
 constexpr int kThreads = kBX * kBY;
-constexpr int kRows = 4;                   // output rows of a lane (argmedian)
-constexpr int kAY = kBY * kRows;           // block rows of the argmedian and of the bit maps
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
 }  // namespace
 
-// One work-group: a 64 x 16 block of one plane, four output rows to a lane.
-// The window union ((64 + k - 1) x (16 + k - 1) values) is staged in LDS as
+// One work-group: a 64 x 4 kRows block of one plane, kRows (four) output rows to
+// a lane. The window union ((64 + k - 1) x (16 + k - 1) values) is staged in LDS as
 // float bits; a row of it that lies in several of the lane's windows is read
 // once and compared with each of their medians. The match of a whole row is
 // one bit per lane, so a comparison is one VALU instruction (its or is
@@ -35,9 +33,14 @@ __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v,
 //
 // Bound: VALU, 1.5 k * k instructions per output. 32x3x512x512: k = 7 0.31 ms with
 // one row to a lane (k * k reads, compares and selects), 0.14 now; k = 15 0.75
-// and 0.37. (A scalar or of the compares' masks instead of v_min3: k = 7 0.15,
-// k = 15 1.31, the masks outgrow the scalar registers.)
-template <int K>
+// and 0.37. Where a wave's medians all lie in the first rows of their windows,
+// as in images of few levels, the wave ends there: it looks once, after eight
+// rows (with the median, two levels, us, a stop at the first match / none /
+// now: 100 x 300 k = 33 28 / 58 / 31, 32 x 512 x 512 k = 15 243 / 296 / 245). Few blocks
+// of a large window take one row to a lane, whose wave ends sooner (100 x 300 k = 25,
+// with the median, noise 52 and 40 us). (A scalar or of the compares' masks
+// instead of v_min3: k = 7 0.15, k = 15 1.31, the masks outgrow the scalar registers.)
+template <int K, int kRows>
 __global__ void __launch_bounds__(kThreads)
 mf_argmedian_kernel(const uint32_t* __restrict__ src, const uint32_t* __restrict__ med,
                     int32_t* __restrict__ idx, int H, int W, int k_rt, int nbx, int nby)
@@ -49,6 +52,7 @@ mf_argmedian_kernel(const uint32_t* __restrict__ src, const uint32_t* __restrict
     const int by = b / nbx, bx = b - by * nbx;
     const int r = (k - 1) / 2;
     const long long base = (long long)plane * H * W;
+    constexpr int kAY = kBY * kRows;
     const int X0 = bx * kBX, Y0 = by * kAY;
     const int lw = kBX + 2 * r, lh = kAY + 2 * r;
     for (int i = threadIdx.x; i < lw * lh; i += kThreads) {
@@ -64,10 +68,11 @@ mf_argmedian_kernel(const uint32_t* __restrict__ src, const uint32_t* __restrict
     for (int j = 0; j < kRows; ++j) {
         const int y = min(Y0 + ty + j, H - 1);
         m[j] = med[base + (long long)y * W + min(x, W - 1)];
-        row[j] = -1;
+        row[j] = x < W && Y0 + ty + j < H ? -1 : 0;
     }
     __syncthreads();
-    for (int t = 0; t < k + kRows - 1; ++t) {
+    if (Y0 + ty >= H) return;  // a whole wave
+    auto scan = [&](int t) {
         const uint32_t* p = tile + (ty + t) * lw + tx;
         uint32_t off[kRows];   // 0 where the row holds the median
 #pragma unroll
@@ -81,7 +86,14 @@ mf_argmedian_kernel(const uint32_t* __restrict__ src, const uint32_t* __restrict
 #pragma unroll
         for (int j = 0; j < kRows; ++j)
             if (t >= j && t - j < k) row[j] = off[j] == 0 && row[j] < 0 ? t - j : row[j];
-    }
+    };
+    const int n = k + kRows - 1, look = k > 7 ? 8 : n;
+    for (int t = 0; t < look; ++t) scan(t);
+    int least = row[0];
+#pragma unroll
+    for (int j = 1; j < kRows; ++j) least = min(least, row[j]);
+    if (!__all(least >= 0))
+        for (int t = look; t < n; ++t) scan(t);
 #pragma unroll
     for (int j = 0; j < kRows; ++j) {
         const int y = Y0 + ty + j;
@@ -105,7 +117,8 @@ mf_argmedian_kernel(const uint32_t* __restrict__ src, const uint32_t* __restrict
 // Bound: instruction issue and LDS latency of the bit loops (a wave runs as
 // long as its most named pixel), from k = 17 on the LDS the maps leave for
 // other work-groups. 32x3x512x512, comparing k * k neighbours and now: k = 7
-// 0.35 and 0.18 ms, k = 15 0.91 and 0.36, k = 31 3.8 and 0.99.
+// 0.35 and 0.18 ms, k = 15 0.91 and 0.36, k = 31 3.8 and 0.99. Small windows of few
+// pixels compare (k = 7, us: 100 x 300 7.2 against 9.3, 512 x 512 8.0 against 9.0).
 template <int RB, int ROWS, int THREADS>
 __global__ void __launch_bounds__(THREADS)
 mf_grad_bits_kernel(const float* __restrict__ gout, const int32_t* __restrict__ idx, float* __restrict__ gin, int H,
@@ -160,7 +173,8 @@ mf_grad_bits_kernel(const float* __restrict__ gout, const int32_t* __restrict__ 
     }
 }
 
-// Windows beyond 31: every q compares the argmedian of its k * k neighbours.
+// Windows beyond 31, and up to 7 with few pixels: every q compares the argmedian
+// of its k * k neighbours.
 __global__ void __launch_bounds__(kThreads)
 mf_grad_gather_kernel(const float* __restrict__ gout, const int32_t* __restrict__ idx,
                       float* __restrict__ gin, int H, int W, int k, int nbx, int nby)
@@ -221,15 +235,17 @@ hipError_t by_planes(int64_t planes, int64_t plane_blocks, int threads, const La
     return hipSuccess;
 }
 
-template <int K>
-hipError_t argmedian(const float* src, const float* med, int32_t* idx, int64_t planes, size_t lds, int H, int W, int k,
-                     int nbx, int nby, hipStream_t stream)
+template <int K, int ROWS>
+hipError_t argmedian(const float* src, const float* med, int32_t* idx, int64_t planes, int H, int W, int k,
+                     hipStream_t stream)
 {
-    hipError_t e = allow_lds(mf_argmedian_kernel<K>, lds);
+    const int nbx = (W + kBX - 1) / kBX, nby = (H + kBY * ROWS - 1) / (kBY * ROWS);
+    const size_t lds = (size_t)(kBX + k - 1) * (kBY * ROWS + k - 1) * 4;
+    hipError_t e = allow_lds(mf_argmedian_kernel<K, ROWS>, lds);
     if (e != hipSuccess) return e;
     return by_planes(planes, (int64_t)nbx * nby, kThreads, [&](int64_t p0, int64_t np) {
         const int64_t o = p0 * H * W;
-        hipLaunchKernelGGL(mf_argmedian_kernel<K>, dim3((unsigned)(np * nbx * nby)), dim3(kThreads), lds, stream,
+        hipLaunchKernelGGL((mf_argmedian_kernel<K, ROWS>), dim3((unsigned)(np * nbx * nby)), dim3(kThreads), lds, stream,
                            (const uint32_t*)src + o, (const uint32_t*)med + o, idx + o, H, W, k, nbx, nby);
     });
 }
@@ -257,13 +273,14 @@ hipError_t grad_bits(const float* gout, const int32_t* idx, float* gin, int64_t 
 hipError_t mf_ag_argmedian_launch(const float* src, const float* med, int32_t* idx, int64_t planes, int H,
                                   int W, int k, hipStream_t stream)
 {
-    const int nbx = (W + kBX - 1) / kBX, nby = (H + kAY - 1) / kAY;
-    const size_t lds = (size_t)(kBX + k - 1) * (kAY + k - 1) * 4;
     switch (k) {
-#define MF_CASE(K) case K: return argmedian<K>(src, med, idx, planes, lds, H, W, k, nbx, nby, stream);
+#define MF_CASE(K) case K: return argmedian<K, 4>(src, med, idx, planes, H, W, k, stream);
     MF_CASE(3) MF_CASE(5) MF_CASE(7) MF_CASE(9) MF_CASE(11) MF_CASE(13) MF_CASE(15)
 #undef MF_CASE
-    default: return argmedian<0>(src, med, idx, planes, lds, H, W, k, nbx, nby, stream);
+    default:
+        return H <= 8 || planes * ((W + kBX - 1) / kBX) * ((H + 15) / 16) <= 256
+                   ? argmedian<0, 1>(src, med, idx, planes, H, W, k, stream)
+                   : argmedian<0, 4>(src, med, idx, planes, H, W, k, stream);
     }
 }
 
@@ -271,9 +288,10 @@ hipError_t mf_ag_grad_launch(const float* gout, const int32_t* idx, float* gin, 
                              int k, hipStream_t stream)
 {
     const int nbx = (W + kBX - 1) / kBX;
-    if (k <= 7) return grad_bits<8, 16, 256>(gout, idx, gin, planes, H, W, k, stream);
-    if (k <= 15) return grad_bits<16, 16, 512>(gout, idx, gin, planes, H, W, k, stream);
-    if (k <= 31) return grad_bits<32, 8, 512>(gout, idx, gin, planes, H, W, k, stream);
+    const bool few = k <= 7 && planes * nbx * ((H + kBY - 1) / kBY) <= 1024;     // work-groups that compare
+    if (k <= 7 && !few) return grad_bits<8, 16, 256>(gout, idx, gin, planes, H, W, k, stream);
+    if (k <= 15 && !few) return grad_bits<16, 16, 512>(gout, idx, gin, planes, H, W, k, stream);
+    if (k <= 31 && !few) return grad_bits<32, 8, 512>(gout, idx, gin, planes, H, W, k, stream);
     const int nby = (H + kBY - 1) / kBY;
     const size_t lds = (size_t)(kBX + k - 1) * (kBY + k - 1) * 8;
     if (lds > 64 * 1024) {
