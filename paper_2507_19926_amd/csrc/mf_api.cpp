@@ -343,23 +343,46 @@ int32_t mf_internal_validate(const void* src, const void* dst, int64_t H, int64_
 
 int32_t mf_internal_fail(int32_t code, const char* msg) { return fail(code, "%s", msg); }
 
-// Which images of a batch are together too few for their histograms: 1, those
-// that would be ranked (below 2^19 pixels: a batched region has 64 rows and takes
-// 75-105 us alone), 2, the 8-bit ones that have a network (below 2^20: each
-// window's histograms are one more kernel of the graph, the networks are shared
-// with the 16-bit images). Batches, with histograms for 8-bit data always and
-// ranks from 2^17 pixels, against these lines: 16 images of up to 512 a side 282
-// / 204 us, 24 305 / 186, 31 of up to 280 176 / 132, 74 of up to 1195 161 / 130;
-// 73 of up to 1197 and 164 of up to 824 the same.
+// Which images of a batch are together too few, or too small, for their
+// histograms: 1, those that would be ranked (below 2^19 pixels: a batched region
+// has 64 rows and takes 75-105 us alone); 2, the 8-bit ones that have a network (a
+// block of 64 rows takes 45 us on a smooth image, 68 on noise; the networks take
+// blocks of 512 x 16 pixels, and at least one's time); 4, the 8-bit ones beyond
+// (below 2^18 pixels); and either of 1 and 4 where the parts of all images by estimate
+// take longer than by the schedules (many tiny images). Plans of one window on
+// noise (smooth images), network or schedule / histograms, us: k = 13, 8 of 512^2 36 /
+// 67 (46), 64 of 256^2 111 / 67 (45), 256 of 64^2 88 / 71 (47); k = 21, 4 of 512^2 74 / 58
+// (49), 256 of 64^2 322 / 65 (53); k = 23, 16 of 64^2 30 / 61, 64 56 / 62, 4 of 256^2 55 / 60 (47).
 int mf_internal_small_batch(const mf_image* imgs, int32_t n)
 {
-    int64_t wide = 0, bytes = 0;
-    for (int i = 0; i < n && (wide < (1 << 19) || bytes < (1 << 20)); ++i) {
-        if (!hist_is_faster(imgs[i].dtype, imgs[i].k)) continue;
-        if (imgs[i].dtype != MF_U8) wide += pixels_of(1, imgs[i].H, imgs[i].W);
-        else if (imgs[i].k <= 21) bytes += pixels_of(1, imgs[i].H, imgs[i].W);
+    struct Network {
+        double us, ps;      // of one block, a pixel of many
+    };
+    static const Network kNetwork[] = {{25, 10.8}, {31, 13.2}, {35, 16.4}, {48, 26.3}, {66, 40.6}};   // k = 13, 15, .. 21
+    int64_t wide = 0, large = 0;
+    double hist[2] = {0, 0}, schedule[2] = {0, 0};       // of 8-bit images without a network, of wider ones
+    double net = 0, net_us = 0, blocks = 0;              // of 8-bit images with one
+    for (int i = 0; i < n; ++i) {
+        const mf_image& m = imgs[i];
+        if (!hist_is_faster(m.dtype, m.k)) continue;
+        if (m.dtype == MF_U8 && m.k <= 21) {
+            const Network& w = kNetwork[(m.k - 13) / 2];
+            net += 1e-6 * w.ps * 512 * 16 * (double)((m.W + 511) / 512 * ((m.H + 15) / 16));
+            net_us = std::max(net_us, w.us);
+            blocks += (double)((m.W + (m.k <= 15 ? 255 : 127)) / (m.k <= 15 ? 256 : 128) * ((m.H + 63) / 64));
+            continue;
+        }
+        const bool u8 = m.dtype == MF_U8;
+        (u8 ? large : wide) += pixels_of(1, m.H, m.W);
+        const AutoEntry* a = auto_entry(m.dtype, m.k);
+        if (a && a->variant != MF_VARIANT_DATA_AWARE) a = nullptr;
+        hist[!u8] += mf_hist_batched_estimate(m.dtype, m.k, (int)m.H, (int)m.W);
+        schedule[!u8] += a ? mf_da_estimate(m.dtype, m.k, a->tw, a->th, a->group, 0, a->form, true, 1, (int)m.H, (int)m.W, 0)
+                           : mf_da_estimate(m.dtype, m.k, 0, 0, 0, 0, 0, false, 1, (int)m.H, (int)m.W, 0);
     }
-    return (wide < (1 << 19) ? 1 : 0) | (bytes < (1 << 20) ? 2 : 0);
+    const double strips = 8 + std::max(1.0, blocks / 512) * (64 + 12) * 0.62;
+    return (wide < (1 << 19) || hist[1] > 0.9 * schedule[1] ? 1 : 0) | (std::max(net_us, 12 + net) < strips ? 2 : 0) |
+           (large < (1 << 18) || hist[0] > 1.1 * schedule[0] ? 4 : 0);
 }
 
 int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t* tw, int32_t* th,
@@ -367,9 +390,10 @@ int32_t mf_internal_resolve(int32_t dtype, int32_t k, int32_t* variant, int32_t*
                             int small)
 {
     const OblEntry* e = nullptr;
-    const bool few = dtype == MF_U8 ? (small & 2) && k <= 21 : (small & 1) != 0;
+    const bool network = dtype == MF_U8 && k <= 21;
+    const bool few = (small & (network ? 2 : dtype == MF_U8 ? 4 : 1)) != 0;
     int32_t rc = resolve(dtype, k, nullptr, variant, tw, th, &e, group, da_form,
-                         !few || !hist_is_faster(dtype, k) ? Small::no : dtype == MF_U8 ? Small::network : Small::schedule);
+                         !few || !hist_is_faster(dtype, k) ? Small::no : network ? Small::network : Small::schedule);
     if (rc) return rc;
     // the column-strip form has no batched kernel: plans use k's default
     // network

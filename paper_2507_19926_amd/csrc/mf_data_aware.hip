@@ -868,12 +868,13 @@ static MfDaArgs da_args(const DaEntry* e, const uint32_t* blob)
 // ps a pixel, fitted to one plane of 2048^2 (uniform noise, normal float32): uint8
 // k = 23 105, 75 448; uint16 k = 23 168, 35 261, 75 764, 19 x 13 132, 31 x 29 283;
 // float32 k = 23 297, 35 424, 75 1444, 19 x 13 202, 31 x 29 420; untuned float32 k = 21 336.
-// A launch takes whole rounds of two work-groups to a CU.
+// A launch takes whole rounds of two work-groups to a CU; cus = 0: an image's share
+// of a launch of many, on 256 CUs.
 double mf_da_estimate(int dtype, int k, int tw, int th, int group, int kh, int form, bool tuned, long long planes, int H,
                       int W, int cus)
 {
     const DaEntry* e = da_find(dtype, k, tw, th, group, kh, form);
-    if (!e || cus < 1) return 0;
+    if (!e) return 0;
     const int bw = e->tw * e->tiles * e->groups;
     const double area = (double)k * e->kh;
     double ps = dtype == MF_U8 ? 100 + 0.13 * area : dtype == MF_U16 ? 120 + 0.16 * area : 150 + 0.3 * area;
@@ -882,6 +883,7 @@ double mf_da_estimate(int dtype, int k, int tw, int th, int group, int kh, int f
         if (!tuned) ps *= 1.3;
     }
     const long long groups = planes * ((W + bw - 1) / bw) * ((H + e->th - 1) / e->th);
+    if (cus < 1) return 1e-6 * ps * (double)groups * bw * e->th;
     const long long rounds = (groups + 2 * cus - 1) / (2 * cus);
     return 8 + 1e-6 * ps * 512 * (double)rounds * bw * e->th;     // 512: those of 256 CUs, which ps is for
 }

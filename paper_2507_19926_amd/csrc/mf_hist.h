@@ -32,6 +32,8 @@ hipError_t mf_hist_launch(const void* src, void* dst, int planes, long long plan
 // Estimated time in us of mf_hist_launch on the current device, good to a
 // quarter, and that device's CUs; 0 where either is not known.
 double mf_hist_estimate(int dtype, int kw, int kh, long long planes, int H, int W, int* cus);
+// The same of an image's part in a batch, on 256 CUs.
+double mf_hist_batched_estimate(int dtype, int k, int H, int W);
 // Batched kernel of the square k x k window (arguments: jobs, njobs, nblocks).
 hipError_t mf_hist_batched(int dtype, int k, MfBatchedKernel* kern);
 

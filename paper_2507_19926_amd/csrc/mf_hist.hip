@@ -189,6 +189,17 @@ double mf_hist_estimate(int dtype, int kw, int kh, long long planes, int H, int 
     return 8 + (double)clocks / 2400 + 12.0 * (double)rounds;
 }
 
+double mf_hist_batched_estimate(int dtype, int k, int H, int W)
+{
+    HistKernelInfo h;
+    if (!find(dtype, k, k, &h)) return 0;
+    const double blocks = (double)((W + h.cols - 1) / h.cols) * ((H + h.rows - 1) / h.rows);
+    const int used = H < h.rows ? H : h.rows;
+    if (dtype == MF_U8) return blocks / 512 * (used + k / 4 + 8) * (0.4 + 0.0096 * k);
+    const double clocks = (dtype == MF_U16 ? 4.0 : 9.0) * (h.cols + k - 1) * (used + k - 1) + 300.0 * k + 1600.0 * used + 5000;
+    return blocks / 256 * (clocks / 2400 + 12);
+}
+
 hipError_t mf_hist_batched(int dtype, int k, MfBatchedKernel* kern)
 {
     HistKernelInfo h;

@@ -76,8 +76,9 @@ struct MfDaArgs {
 hipError_t mf_da_batched(int dtype, int k, int tw, int th, int group, MfBatchedKernel* kern, MfDaArgs* args,
                          int form = 0);
 
-// Estimated time in us of mf_da_launch on `cus` CUs, from the work-groups it
-// takes; good to a quarter, for choices of a kernel. tuned: the tile is one that
+// Estimated time in us of mf_da_launch on `cus` CUs (0: of its part in a batch,
+// on 256), from the work-groups it takes; good to a quarter, for choices of a
+// kernel. tuned: the tile is one that
 // was chosen by measurement.
 double mf_da_estimate(int dtype, int k, int tw, int th, int group, int kh, int form, bool tuned, long long planes, int H,
                       int W, int cus);

@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2507_19926_amd import _lib
 from paper_2507_19926_amd import workloads as wl
-from paper_2507_19926_amd.ops import median_filter, median_filter_3d, median_filter_rect
+from paper_2507_19926_amd.ops import BatchedPlan, median_filter, median_filter_3d, median_filter_rect
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +58,19 @@ def test_boxes_of_few_voxels(k, shape):
     vol = wl.uniform_plane(D * H, W, np.uint8, seed=k).reshape(shape)
     got = median_filter_3d(torch.from_numpy(vol).cuda(), k).cpu().numpy()
     assert np.array_equal(got, oracle.median_filter_3d(vol, k))
+
+
+@pytest.mark.parametrize("dtype,k,n,H,W", [(np.uint8, 13, 8, 260, 500), (np.uint8, 13, 130, 70, 250), (np.uint8, 21, 200, 60, 64),
+                                           (np.uint8, 23, 16, 64, 64), (np.uint8, 35, 70, 65, 66), (np.uint8, 25, 1100, 16, 16),
+                                           (np.uint16, 25, 2100, 16, 16), (np.uint16, 23, 36, 130, 130), (np.float32, 25, 900, 16, 40)])
+def test_batches_of_small_images(dtype, k, n, H, W):
+    img = _planes(dtype, n, H, W, seed=k)
+    xs = [torch.from_numpy(a).cuda() for a in img]
+    outs = [torch.empty_like(x) for x in xs]
+    plan = BatchedPlan(xs, outs, [k] * n)
+    plan.launch()
+    got = torch.stack([o.view(torch.uint8) for o in outs]).cpu().numpy()
+    plan.close()
+    want = median_filter(torch.from_numpy(img).cuda(), k).cpu().numpy()
+    assert got.tobytes() == want.tobytes()
+    _sampled(img, k, k, want)
