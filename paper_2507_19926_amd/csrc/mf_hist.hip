@@ -33,7 +33,7 @@ bool find(int dtype, int kw, int kh, HistKernelInfo* k)
         return dtype == MF_U16 ? mf_rank_kernel_u16(kw, k) : mf_rank_kernel_u32(kw, k);
     }
     if (kh > 255) return false;
-    if (one_word(kw, kh) && kw <= 31) return mf_hist_kernel_p1(kw, k);
+    if (one_word(kw, kh) && mf_hist_kernel_p1(kw, k)) return true;
     return kw <= 31 ? mf_hist_kernel_p2(kw, k) : mf_hist_kernel_wide(kw, k);
 }
 

@@ -14,7 +14,7 @@ bool mf_rank_kernel_u32(int kw, HistKernelInfo* k)
     case 13: *k = rank_kernel<13, 31, uint32_t, false>(); return true;
     case 15: *k = rank_kernel<15, 31, uint32_t, false>(); return true;
     case 17: *k = rank_kernel<17, 31, uint32_t, false>(); return true;
-    case 19: *k = rank_kernel<19, 31, uint32_t, true>(); return true;
+    case 19: *k = rank_kernel<19, 31, uint32_t, false>(); return true;
     case 21: *k = rank_kernel<21, 31, uint32_t, true>(); return true;
     case 23: *k = rank_kernel<23, 31, uint32_t, true>(); return true;
     case 25: *k = rank_kernel<25, 31, uint32_t, true>(); return true;

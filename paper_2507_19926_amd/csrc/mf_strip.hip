@@ -30,7 +30,6 @@
 namespace {
 
 constexpr int kStripRows = 4;      // output rows per wave
-constexpr int kStripDepth = 6;     // input rows loaded ahead of their use: all
 constexpr int kStripWaves = 4;     // waves per work-group, stacked vertically
 
 __device__ __forceinline__ uint32_t smin(uint32_t a, uint32_t b) { return a < b ? a : b; }
@@ -129,7 +128,6 @@ mf_strip3_kernel(const unsigned char* __restrict__ src, unsigned char* __restric
     constexpr int P = CB / ES;               // pixels per lane
     constexpr int R = kStripRows;
     constexpr int NR = R + 2;                // input rows of a wave
-    constexpr int D = kStripDepth;           // input rows in flight ahead of use
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int bx = blockIdx.x % nbx, by = by0 + (int)(blockIdx.x / nbx);
     const int x0 = bx * 64 * P + lane * P;    // first pixel of this lane's chunk
@@ -173,18 +171,17 @@ mf_strip3_kernel(const unsigned char* __restrict__ src, unsigned char* __restric
         if (edge_lane) h = strip_load1<ES>(row, hx);
     };
 
-    // ring of the next D input rows, loaded D rows ahead of their use
-    Chunk<CB> ring[D];
-    uint32_t hring[D];
+    // all input rows, loaded ahead of their use
+    Chunk<CB> rows[NR];
+    uint32_t hrows[NR];
 #pragma unroll
-    for (int i = 0; i < D && i < NR; ++i) load_row(i, ring[i], hring[i]);
+    for (int i = 0; i < NR; ++i) load_row(i, rows[i], hrows[i]);
 
     // input row i as P + 2 keys: [0] = column x0-1, [1..P] = the chunk,
     // [P+1] = column x0+P; pixels past the row's end repeat column W-1
     auto unpack = [&](int i, uint32_t* v) {
-        const Chunk<CB> q = ring[i % D];
-        const uint32_t hq = hring[i % D];
-        if (i + D < NR) load_row(i + D, ring[i % D], hring[i % D]);
+        const Chunk<CB> q = rows[i];
+        const uint32_t hq = hrows[i];
 #pragma unroll
         for (int e = 0; e < P; ++e) {
             const uint32_t u = strip_elem<ES, CB>(q, e);
