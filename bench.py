@@ -68,9 +68,9 @@ def algorithmic_ops_per_pixel(dtype_code: int, k: int, kh: int | None = None):
     (max of minima, median of medians, min of maxima, median of the three);
     these are 32-bit lane-ops, one element each.
 
-    Sliding histograms (data-aware form 3): no min/max; "hist" in place of
-    the packed flag and the LDS counter updates per pixel, 2 (kw + 3) per
-    group of four pixels.
+    Sliding histograms (data-aware form 3, with ranks for 16- and 32-bit
+    data): no min/max; "hist" in place of the packed flag and the LDS counter
+    updates per pixel, 2 (kw + 3) per group of four pixels.
 
     Data-aware: two lane-ops per merge output (the compare that picks the
     smaller head and the min that produces it) plus two per compare-exchange
@@ -126,11 +126,23 @@ def roofline(dtype_code: int, k: int, pixels_per_launch: int, launch_s: float, k
     bytes_per_launch = 2 * es * pixels_per_launch
     variant, tile, ops_px, packed = algorithmic_ops_per_pixel(dtype_code, k, kh)
     if packed == "hist":
-        # a counter update reads and writes one LDS word
-        achieved = 8.0 * ops_px * pixels_per_launch / launch_s
-        return {"bound": "lds", "achieved": achieved / 1e12, "peak": LDS_PEAK_BPS / 1e12, "unit": "TB/s",
-                "frac": achieved / LDS_PEAK_BPS, "traffic": None, "lds_updates_per_pixel": ops_px,
-                "variant": variant, "tile": list(tile)}
+        # Against the LDS figure, though the chain of dependent LDS accesses of a
+        # row step takes the time ("limit"), but for wide windows of 8-bit data. A
+        # counter update reads and writes one LDS word. Ranked data are sorted
+        # first, by regions of 128 x 64 outputs, four bits a pass; a pass reads and
+        # writes every value of a region's footprint with its position (one word for
+        # 16-bit data, two for 32-bit).
+        lds = 8.0 * ops_px
+        r = {"bound": "lds", "unit": "TB/s", "peak": LDS_PEAK_BPS / 1e12, "traffic": None,
+             "limit": "latency of the row steps" if k < 50 else "LDS updates", "lds_updates_per_pixel": ops_px,
+             "variant": variant, "tile": list(tile)}
+        if es > 1:
+            sorted_px = (128 + k - 1) * (64 + (kh or k) - 1) / (128 * 64)
+            lds += sorted_px * 2 * es * 2 * (4 if es == 2 else 8)
+            r["limit"] = "latency of a region's sort, row steps and walk"
+            r["sorted_values_per_pixel"] = round(sorted_px, 3)
+        achieved = lds * pixels_per_launch / launch_s
+        return {**r, "achieved": achieved / 1e12, "frac": achieved / LDS_PEAK_BPS}
     valu_peak = VALU_LANES_PER_S * (2 if packed else 1)    # element-ops/s
     t_hbm = bytes_per_launch / HBM_PEAK_BPS
     t_alu = (ops_px * pixels_per_launch / valu_peak) if ops_px else 0.0
@@ -244,7 +256,7 @@ def run_extras(args, dev, stream):
             r = roofline(code, k, side * side, t)
             res[str(k)] = {"mpix_s": round(side * side / t / 1e6, 1), "kernel_ms_median": round(t * 1e3, 4),
                            "bound": r["bound"], "frac": round(r["frac"], 4), "variant": r["variant"],
-                           "tile": r["tile"]}
+                           "tile": r["tile"], **({"limit": r["limit"]} if "limit" in r else {})}
         res["buffer_sets"] = nsets
         res["working_set_MB"] = round(nsets * pair_bytes / 1e6, 1)
         sweep[name] = res

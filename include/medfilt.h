@@ -80,7 +80,7 @@ typedef struct mf_options {
                          shared by the tiles, 2 = each tile sorts its own
                          columns (small k), 3 = column-strip streaming form
                          (k = 3 only: root tile 1x1, each sorted column
-                         shared by three windows, rows streamed through
+                         shared by three windows, a strip's rows in
                          registers); data-aware: 1 = rounds per recursion
                          level, 2 = rounds over the whole schedule, 3 =
                          sliding histograms (root tile 1x1; where they are
@@ -88,8 +88,9 @@ typedef struct mf_options {
                          32-bit k >= 21; not among the configurations that
                          mf_list_configs enumerates, as there is nothing in
                          them to tune; by default 16- and 32-bit calls of
-                         fewer than 131072 pixels run the schedule
-                         instead); 0 = library's                            */
+                         fewer than 131072 pixels, and narrow images
+                         and many tiny planes of any type, run the
+                         schedule where that is faster); 0 = library's      */
     int32_t rows;     /* oblivious: tile rows per wave; 0 = library's       */
 } mf_options;
 
@@ -151,7 +152,7 @@ int32_t mf_max_rect_side(void);
  * MF_VARIANT_OBLIVIOUS and the network's root tile when one is compiled for
  * the shape, else MF_VARIANT_DATA_AWARE and the generated schedule's tile
  * (MF_VARIANT_AUTO runs such shapes by sliding histograms for all but small
- * images, MF_VARIANT_DATA_AWARE by the schedule). Errors as
+ * or narrow images, MF_VARIANT_DATA_AWARE by the schedule). Errors as
  * median_filter_rect's window and dtype checks (MF_ERR_NULL for a NULL
  * output pointer). */
 int32_t mf_query_rect_config(int32_t dtype, int32_t kw, int32_t kh, int32_t* variant,

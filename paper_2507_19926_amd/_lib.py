@@ -132,7 +132,8 @@ def options(variant: int = MF_VARIANT_AUTO, tile=None, group: int = 0, form: int
 
 
 def list_configs(dtype_code: int, k: int):
-    """Every compiled (variant, tile_w, tile_h, group, form, rows) for dtype and k, default first."""
+    """Every compiled (variant, tile_w, tile_h, group, form, rows) for dtype and k.
+    The sliding histograms, which have nothing to tune, are not among them."""
     L = lib()
     n = L.mf_list_configs(dtype_code, k, None, 0)
     if n < 0:

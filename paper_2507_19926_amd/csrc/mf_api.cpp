@@ -120,11 +120,12 @@ const OblEntry* find_obl(int k, int tw, int th, int nw, int form, int rows)
 
 // Square windows that run the sliding-histogram form: 8-bit data from k = 13
 // on. Its time hardly depends on k but does on the data (the search
-// walks from one row's median to the next, far on noise with a small window).
-// Per 30 MP RGB frame, smooth image / uniform noise against the network or
-// the schedule: k = 11 0.36 / 0.79 ms against 0.55 ms; k = 15 0.42 / 0.70
-// against 1.14; k = 17 0.54 / 0.96 against 1.41; k = 25 0.70 / 0.97 against
-// 10.4; k = 75 1.42 / 1.43 against 40.
+// walks from one row's median to the next, far on noise and two levels). One
+// plane of 4480 x 6720, us, smooth / noise / two levels against the network:
+// k = 13 131 / 234 / 277 against 325, k = 17 195 / 285 / 473 against 495, k = 21
+// two levels 494 against 1226; k = 11, where all three planes take 0.36 ms smooth
+// and 0.79 on noise, has a network of 0.45. 30 MP RGB by schedule and now:
+// k = 25 10.4 / 0.65 ms, k = 75 40 / 1.39.
 // 16- and 32-bit data rank the values first, so their line lies where the
 // networks end or slow down (4096^2, uniform 16-bit and normal float32 data):
 // 16-bit k = 21 0.70 ms against the network's 0.67, k = 25 0.63 against 3.2

@@ -16,7 +16,7 @@
 // Counter words: P = 1 holds all seven counts in 32 bits (8 shared, six of 4;
 // windows of up to 15 rows and 255 shared values), 64 groups to a
 // work-group; P = 2 in 64 bits (16 shared, six of 8), 32 groups. Either way
-// 64 KB of counters, two work-groups per CU. A field may overflow between an
+// 64 KB of counters and 4 KB for 16 bins each, two work-groups per CU. A field may overflow between an
 // addition and the removal that follows it: words are added modulo 2^32, so
 // they are exact when read. Bin v of group g lies at 256 v + 128 p + 4 g:
 // the address of a pixel's counter is one v_perm_b32 (pixel byte above the
@@ -26,14 +26,16 @@
 // a row). A search wave starts at the last median's bin: it knows how many
 // window values lie below that bin (the rows that came and went are counted
 // against it, four bytes at a time, by v_lerp_u8's carry) and walks up or
-// down from it, four bins and then eight at a time. A slide wave holds the
-// addresses of its counters ready while the others search.
+// down from it, four bins and then eight at a time. Where the walks are long
+// (two levels, noise), counters of 16 bins are kept too and searched instead
+// (see rows()). A slide wave holds the addresses of its counters ready while
+// the others search.
 //
 // Bound: the row step's latency (a barrier, the dependent search, a barrier,
 // the atomics), overlapped between the two work-groups of a CU; from about
 // k = 50 on the LDS atomics (4.0 clocks of the CU for each wave's, 14.6 for one
 // wave alone). Per 30 MP RGB frame (smooth image), before (network, schedule)
-// and now: k = 17 1.41 / 0.54 ms, k = 25 10.4 / 0.70, k = 75 40.2 / 1.42.
+// and now: k = 17 1.41 / 0.56 ms, k = 25 10.4 / 0.65, k = 75 40.2 / 1.39.
 #pragma once
 
 #include <type_traits>

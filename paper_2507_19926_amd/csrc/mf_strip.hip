@@ -13,7 +13,7 @@
 // Each wave owns a strip of 64 lanes x P pixels (one 16-byte chunk per lane and
 // row, 8 bytes for small 8-bit images) and R = 4 output rows. A lane loads the
 // R + 2 input rows of its chunk into registers at once (no LDS, no barriers),
-// keeps three rows and a sliding window of three sorted columns, and stores
+// goes down them with a sliding window of three sorted columns, and stores
 // each output row as one chunk. The columns just left and right of a lane's
 // chunk come from the neighbouring lanes by a lane shuffle; lanes 0 and 63
 // load theirs. A work-group stacks 4 waves vertically.
